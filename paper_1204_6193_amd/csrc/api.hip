@@ -706,7 +706,7 @@ rngx_status ising_create(uint32_t L, rngx_kind kind, uint64_t seed, rngx_ising *
     hipError_t e = hipMalloc(&lat->d_spins, static_cast<size_t>(L) * L);
     if (e == hipSuccess) e = hipMalloc(&lat->d_err, 4);
     if (e == hipSuccess && lat->plan.strips && lat->plan.nwg > 1) {
-        e = hipMalloc(&lat->d_halo, static_cast<size_t>(8) * lat->plan.nwg * L);
+        e = hipMalloc(&lat->d_halo, halo_bytes(lat->plan.nwg, L));
         lat->halo_nwg = lat->plan.nwg;
     }
     // partials of the per-pass path (lagged Fibonacci multi-hit sweeps take it under any plan)
@@ -720,7 +720,7 @@ rngx_status ising_create(uint32_t L, rngx_kind kind, uint64_t seed, rngx_ising *
     if (e == hipSuccess) e = launch_hot_start(lat, seed, nullptr);
     if (e == hipSuccess) e = launch_zero(lat->d_err, 1, nullptr);
     if (e == hipSuccess && lat->d_halo)  // tag 0 matches no pass
-        e = launch_zero(reinterpret_cast<uint32_t *>(lat->d_halo), 2ull * lat->plan.nwg * L, nullptr);
+        e = launch_zero(reinterpret_cast<uint32_t *>(lat->d_halo), halo_bytes(lat->plan.nwg, L) / 4, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
         free_ising(lat);
@@ -772,13 +772,13 @@ hipError_t apply_plan(Ising *lat, const IsingPlan &p) {
         (void)hipFree(lat->d_halo);
         lat->d_halo = nullptr;
         lat->halo_nwg = 0;
-        e = hipMalloc(&lat->d_halo, 8ull * p.nwg * L);
+        e = hipMalloc(&lat->d_halo, halo_bytes(p.nwg, L));
         if (e == hipSuccess) lat->halo_nwg = p.nwg;
     }
     if (e == hipSuccess && (!p.strips || is_lfg(lat->gen->kind)) && !lat->d_partial)
         e = hipMalloc(&lat->d_partial, 4 * ising_partials(lat->L));
     if (e == hipSuccess && lat->d_halo)
-        e = launch_zero(reinterpret_cast<uint32_t *>(lat->d_halo), 2ull * lat->halo_nwg * L, nullptr);
+        e = launch_zero(reinterpret_cast<uint32_t *>(lat->d_halo), halo_bytes(lat->halo_nwg, L) / 4, nullptr);
     if (e == hipSuccess) e = launch_zero(lat->d_err, 1, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return e;

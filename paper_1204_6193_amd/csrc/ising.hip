@@ -5,14 +5,14 @@
 // pass c it updates sites x0 + ((c+y)&1) and x0 + 2 + ((c+y)&1) with its next
 // two outputs (XS1024W: one lane pair = streams 2u, 2u+1 = an 8-site run).
 //
-// Strip kernel (L up to ~5800): the lattice is cut into horizontal strips of
-// R rows, one workgroup each.  A workgroup keeps its strip's spins in LDS and
-// its streams' state in VGPRs for all sweeps of the call; only the two
-// boundary rows of a strip go through global memory after each pass, and
-// neighbouring strips synchronise through per-strip flags (release/acquire at
-// agent scope).  Cooperative launch guarantees that every strip is resident,
-// so every wait ends; the waits are also bounded.  A lattice that fits one
-// workgroup (one strip, R = L) wraps its halo rows inside LDS.
+// Strips (L up to ~5800): the lattice is cut into horizontal strips of R
+// rows, one workgroup each, that keep their streams' state in VGPRs for all
+// sweeps of the call; only the two boundary rows of a strip go through global
+// memory after each pass, as tagged words that the neighbours poll.
+// Cooperative launch guarantees that every strip is resident, so every wait
+// ends; the waits are also bounded.  The spins are bits in registers
+// (ising_bits.h) where a strip's rows divide over its threads so (bits_shape),
+// else, and for the lagged Fibonacci kinds, bytes in LDS (k_ising_strip).
 //
 // Per-pass kernels (larger L): one launch per colour pass, state and spins
 // streamed from memory, energy reduced per block and then across blocks.
@@ -25,17 +25,19 @@
 // end, so E = -sum over colour-1 sites of s h = -sum (4 - 2 m_after).
 #include <algorithm>
 #include <cmath>
+#include <map>
+#include <mutex>
 #include <numeric>
+#include <tuple>
 #include <type_traits>
 #include <vector>
 
-#include "rngx_internal.h"
+#include "ising_device.h"
 
 namespace rngx {
 
 namespace {
 
-constexpr int kBlock = 256;
 constexpr uint64_t kOnes8 = 0x0101010101010101ull;
 
 __global__ __launch_bounds__(kBlock) void k_hot_start(int8_t *spins, uint64_t n_words, uint64_t seed) {
@@ -90,201 +92,6 @@ __device__ __forceinline__ void hit_mem(uint32_t &mi, uint32_t &flip, uint32_t r
     flip ^= acc ? 1u : 0u;
 }
 
-// ---------------------------------------------------------------- units
-// A unit is what one thread updates with one set of draws: a stream (4
-// sites) for the small-state kinds, a lane pair of an XS1024W instance (8
-// sites) for the paper's generator.  Units are numbered like the stream
-// (small kinds) or stream/2 (XS1024W).
-template <class G>
-struct SmallUnit {
-    static constexpr int kNB = 4;
-    G g;
-    __device__ void load(const uint8_t *st, uint64_t S, uint64_t u) { g.load(st, S, u); }
-    __device__ void store(uint8_t *st, uint64_t S, uint64_t u, uint64_t) const { g.store(st, S, u); }
-    __device__ void draw(uint32_t (&r)[2]) { r[0] = g.next(); r[1] = g.next(); }
-    // multi-hit updates: n draws in order to f0, then n more to f1
-    template <class F0, class F1>
-    __device__ void draws2(uint32_t n, F0 &&f0, F1 &&f1) {
-        for (uint32_t i = 0; i < n; ++i) f0(g.next());
-        for (uint32_t i = 0; i < n; ++i) f1(g.next());
-    }
-};
-
-// Philox with only key and position held: the two draws of a pass come from
-// one block unless they straddle a block boundary.
-template <int ROUNDS>
-struct PhiloxUnitR {
-    static constexpr int kNB = 4;
-    uint32_t k0, k1;
-    uint64_t pos;
-    __device__ void load(const uint8_t *st, uint64_t S, uint64_t u) {
-        const uint32_t *p = reinterpret_cast<const uint32_t *>(st);
-        k0 = p[u]; k1 = p[S + u];
-        pos = reinterpret_cast<const uint64_t *>(st + 8 * S)[u];
-    }
-    __device__ void store(uint8_t *st, uint64_t S, uint64_t u, uint64_t) const {
-        reinterpret_cast<uint64_t *>(st + 8 * S)[u] = pos;
-    }
-    __device__ void draw(uint32_t (&r)[2]) {
-        uint32_t b0, b1, b2, b3;
-        philox_block<ROUNDS>(k0, k1, pos >> 2, b0, b1, b2, b3);
-        const uint32_t j = static_cast<uint32_t>(pos) & 3;
-        r[0] = j == 0 ? b0 : j == 1 ? b1 : j == 2 ? b2 : b3;
-        if (j == 3) philox_block<ROUNDS>(k0, k1, (pos >> 2) + 1, b0, b1, b2, b3);
-        r[1] = j == 0 ? b1 : j == 1 ? b2 : j == 2 ? b3 : b0;
-        pos += 2;
-    }
-    // as SmallUnit::draws2, in one loop so that a block serves four draws in
-    // a row also across the two runs
-    template <class F0, class F1>
-    __device__ void draws2(uint32_t n, F0 &&f0, F1 &&f1) {
-        uint32_t b0 = 0, b1 = 0, b2 = 0, b3 = 0;
-        for (uint32_t i = 0; i < 2 * n; ++i) {
-            const uint32_t j = static_cast<uint32_t>(pos) & 3;
-            if (i == 0 || j == 0) philox_block<ROUNDS>(k0, k1, pos >> 2, b0, b1, b2, b3);
-            const uint32_t r = j == 0 ? b0 : j == 1 ? b1 : j == 2 ? b2 : b3;
-            if (i < n) f0(r);
-            else f1(r);
-            ++pos;
-        }
-    }
-};
-using PhiloxUnit = PhiloxUnitR<10>;
-using PhiloxUnit7 = PhiloxUnitR<7>;
-
-// Philox in a strip whose streams all stand at the same block boundary at
-// the start of a call (the usual case: seeded at 0, and every call advances
-// every stream by the same multiple of 4).  A sweep takes the four words of
-// one block: the colour-0 pass makes block blk0 + t, uses words 0 and 1 and
-// keeps 2 and 3 for the colour-1 pass, so each block is made once rather
-// than once per pass, and the position, the same for all units, is not held
-// per unit.
-template <int ROUNDS>
-struct PhiloxSweepUnitR {
-    static constexpr int kNB = 4;
-    uint32_t k0, k1, c2, c3;
-    __device__ void load(const uint8_t *st, uint64_t S, uint64_t u) {
-        const uint32_t *p = reinterpret_cast<const uint32_t *>(st);
-        k0 = p[u]; k1 = p[S + u];
-        c2 = c3 = 0;
-    }
-    template <class Args>
-    __device__ void store_at(uint8_t *st, uint64_t S, uint64_t u, const Args &g) const {
-        reinterpret_cast<uint64_t *>(st + 8 * S)[u] = 4 * (g.blk0 + g.n_sweeps);
-    }
-    template <class Args>
-    __device__ void draw_at(uint32_t (&r)[2], const Args &g, uint64_t sweep, int c) {
-        if (c == 0) {
-            philox_block<ROUNDS>(k0, k1, g.blk0 + sweep, r[0], r[1], c2, c3);
-        } else {
-            r[0] = c2;
-            r[1] = c3;
-        }
-    }
-};
-template <class Unit> struct SweepCounter : std::false_type {};  // units that derive their pass from the call's start
-template <int ROUNDS> struct SweepCounter<PhiloxSweepUnitR<ROUNDS>> : std::true_type {};
-
-// Lagged Fibonacci units in strips (single-hit).  A strip holds whole
-// instances (1024 units each) and runs 1024 threads, so slot i of thread t is
-// stream t of the strip's instance i.  Before each colour pass the workgroup
-// makes that pass's two rows of every instance of the strip in LDS rings of B
-// words (value v at v mod B; runs of at most kRun values, a barrier each,
-// whose reads and writes never share a ring word) and each thread takes
-// value t of both rows for every slot; the unit only hands them out, in the
-// order of the per-pass path (row 1 to the first colour-c site, row 2 to the
-// second).
-template <int LR, int LS>
-struct LfgStripUnit {
-    static constexpr int kNB = 4;
-    static constexpr uint32_t kR = LR, kS = LS;
-    static constexpr uint32_t B = LR < 1024 ? 1024 : 2048;
-    static constexpr uint32_t kRun = (B - LR) < static_cast<uint32_t>(LS) ? B - LR : LS;
-    static_assert(B >= LR + 1 && kRun >= 1, "ring too small");
-    uint32_t d0, d1;
-    __device__ void load(const uint8_t *, uint64_t, uint64_t) {}
-    __device__ void store(uint8_t *, uint64_t, uint64_t, uint64_t) const {}
-    __device__ void draw(uint32_t (&r)[2]) { r[0] = d0; r[1] = d1; }
-};
-template <class Unit> struct IsLfgStrip : std::false_type {};
-template <int LR, int LS> struct IsLfgStrip<LfgStripUnit<LR, LS>> : std::true_type {};
-// LDS of the rings of a strip's instances (after the strip's own bytes).
-template <class Unit>
-__host__ __device__ constexpr uint64_t lfg_ring_bytes(uint32_t units) {
-    if constexpr (IsLfgStrip<Unit>::value) return 4ull * Unit::B * (units / 1024) + 16;
-    else return 0;
-}
-
-// XS1024W lane pair u: lane u%16 of instance u/16 of the handle (words 2u,
-// 2u+1 = streams 2u and 2u+1).  Two instance steps per pass; the draws are
-// ordered stream 2u first, stream 2u+1 second, each in step order.
-struct XsUnit {
-    static constexpr int kNB = 8;
-    uint32_t a, b, y;
-    __device__ void load(const uint8_t *st, uint64_t S, uint64_t u) {
-        const uint2 w = reinterpret_cast<const uint2 *>(st)[u];
-        a = w.x; b = w.y;
-        const uint64_t n = reinterpret_cast<const uint64_t *>(st + 4 * S)[u >> 4];
-        y = *reinterpret_cast<const uint32_t *>(st + 4 * S + 8 * (S / 32)) + static_cast<uint32_t>(n) * kWeylC;
-    }
-    __device__ void store(uint8_t *st, uint64_t S, uint64_t u, uint64_t steps) const {
-        reinterpret_cast<uint2 *>(st)[u] = make_uint2(a, b);
-        if ((u & 15) == 0) reinterpret_cast<uint64_t *>(st + 4 * S)[u >> 4] += steps;
-    }
-    __device__ void draw(uint32_t (&r)[4]) {
-        xs1024_step(a, b);
-        y += kWeylC;
-        uint32_t m = weyl_mix(y);
-        r[0] = a + m; r[2] = b + m;
-        xs1024_step(a, b);
-        y += kWeylC;
-        m = weyl_mix(y);
-        r[1] = a + m; r[3] = b + m;
-    }
-    // one instance step: the next draw of stream 2u (ra) and of 2u+1 (rb)
-    __device__ void pair(uint32_t &ra, uint32_t &rb) {
-        xs1024_step(a, b);
-        y += kWeylC;
-        const uint32_t m = weyl_mix(y);
-        ra = a + m;
-        rb = b + m;
-    }
-};
-
-// XS1024W in a strip whose instances have all taken the same number of
-// steps at the start of a call (the usual case: every call advances every
-// instance alike).  The Weyl word of a pass is then the same for every unit:
-// it follows from the call's start (step count blk0, Weyl word y_start) and
-// the sweep, instead of being held and stepped per unit.
-struct XsSweepUnit {
-    static constexpr int kNB = 8;
-    uint32_t a, b;
-    __device__ void load(const uint8_t *st, uint64_t, uint64_t u) {
-        const uint2 w = reinterpret_cast<const uint2 *>(st)[u];
-        a = w.x; b = w.y;
-    }
-    template <class Args>
-    __device__ void store_at(uint8_t *st, uint64_t S, uint64_t u, const Args &g) const {
-        reinterpret_cast<uint2 *>(st)[u] = make_uint2(a, b);
-        if ((u & 15) == 0) reinterpret_cast<uint64_t *>(st + 4 * S)[u >> 4] = g.blk0 + 4 * g.n_sweeps;
-    }
-    // as XsUnit::draw for the pass (sweep, c): 4 sweep + 2 c steps after the start
-    template <class Args>
-    __device__ void draw_at(uint32_t (&r)[4], const Args &g, uint64_t sweep, int c) {
-        const uint32_t y = g.y_start + static_cast<uint32_t>(4 * sweep + 2 * c) * kWeylC;
-        xs1024_step(a, b);
-        uint32_t m = weyl_mix(y + kWeylC);
-        r[0] = a + m; r[2] = b + m;
-        xs1024_step(a, b);
-        m = weyl_mix(y + 2 * kWeylC);
-        r[1] = a + m; r[3] = b + m;
-    }
-};
-template <> struct SweepCounter<XsSweepUnit> : std::true_type {};
-template <class Unit> struct SweepOf { using type = void; };  // the sweep form of a unit, if it has one
-template <int ROUNDS> struct SweepOf<PhiloxUnitR<ROUNDS>> { using type = PhiloxSweepUnitR<ROUNDS>; };
-template <> struct SweepOf<XsUnit> { using type = XsSweepUnit; };
-
 template <int NB>
 __device__ __forceinline__ uint64_t lds_run(const uint8_t *p) {
     if constexpr (NB == 8) return *reinterpret_cast<const uint64_t *>(p);
@@ -316,46 +123,6 @@ struct ReplicaDesc {
     uint32_t *gang;   // strips: arrival counter of the gang's workgroups (zeroed before each run)
     uint64_t start_ticks;  // strips: wall-clock ticks a gang member waits for the others to start
 };
-
-struct StripArgs {
-    int8_t *spins;
-    uint8_t *st;
-    uint64_t S;
-    uint32_t L, R, nwg, units;  // units per strip
-    uint64_t T4, T8, n_sweeps;
-    int32_t *trace;             // may be null
-    uint64_t *halo;             // 2 slots x nwg x 2 rows x L/4 tagged words
-    uint32_t epoch0;            // pass tags of this call are epoch0 + 1, epoch0 + 2, ...
-    uint32_t *err;
-    uint32_t hits;              // Metropolis updates per visited site (multi-hit kernels)
-    uint32_t R0;                // rows of every strip but the last: strip r starts at row r*R0
-    uint64_t blk0;              // sweep forms, at the start: Philox the common block index, XS1024W the step count
-    uint32_t y_start;           // sweep-form XS1024W: the common Weyl word at the start
-};
-
-constexpr uint32_t kSpinLimit = 1u << 20;
-
-// Halo words: 4 spins in the low half, the pass tag in the high half, both
-// written by one 64-bit agent-scope atomic store, so a word read with the
-// expected tag holds that pass's spins.  Polls one word until its tag is
-// `tag`; gives up after kSpinLimit polls and records that in *err (once set,
-// every later poll returns at once, so a failed exchange ends the kernel
-// quickly with an invalid lattice instead of stalling it).
-__device__ __forceinline__ uint32_t poll_word(const uint64_t *p, uint64_t v, uint32_t tag, uint32_t *err) {
-    for (uint32_t it = 0; static_cast<uint32_t>(v >> 32) != tag; ++it) {
-        if (it >= kSpinLimit || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-            __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-        v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    return static_cast<uint32_t>(v);
-}
-
-__device__ __forceinline__ void put_word(uint64_t *p, uint32_t spins, uint32_t tag) {
-    __hip_atomic_store(p, (static_cast<uint64_t>(tag) << 32) | spins, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // Two rows of L bytes (src0 -> dst0, src1 -> dst1) by the whole block: all
 // loads are issued before the first LDS write, one round trip in all.
@@ -397,20 +164,6 @@ __host__ __device__ constexpr uint32_t lds_pitch(uint32_t L) { return L + 2 * kP
 // and a zero word.
 __host__ __device__ constexpr uint64_t strip_lds_bytes(uint32_t L, uint32_t R) {
     return static_cast<uint64_t>(R + 4) * lds_pitch(L) + 80;
-}
-
-// Acceptance in 32 bits.  With d = twice the number of a site's neighbours
-// that differ from it (0, 2, .., 8), the flip is taken if d >= lo, else iff
-// r < (d == 2 ? t4 : t8).  lo is 4 except when a threshold is 2^32 (every
-// draw accepts), which 32 bits cannot hold: lo = 2 when that is T4, lo = 0
-// when it is T8 (and then also T4, since T8 <= T4).
-struct Accept {
-    uint32_t t4, t8, lo;
-};
-__device__ __forceinline__ Accept make_accept(uint64_t T4, uint64_t T8) {
-    constexpr uint64_t kAll = 1ull << 32;
-    return Accept{T4 >= kAll ? 0xFFFFFFFFu : static_cast<uint32_t>(T4), T8 >= kAll ? 0xFFFFFFFFu : static_cast<uint32_t>(T8),
-                  T8 >= kAll ? 0u : T4 >= kAll ? 2u : 4u};
 }
 
 // Twice the number of differing neighbours of each byte of a 4-spin word w
@@ -852,32 +605,6 @@ __device__ __forceinline__ void strip_body(const StripArgs &a, uint32_t r, uint8
             else u[i].store(a.st, a.S, ubase + k, 4 * a.n_sweeps * (MH ? a.hits : 1));
         }
     }
-}
-
-// Whether every stream of strip r stands at the same position, a multiple of
-// 4 (Philox): then *blk0 is that position's block.
-__device__ inline bool strip_positions_aligned(const StripArgs &a, uint32_t r, uint64_t *blk0) {
-    const uint64_t ubase = static_cast<uint64_t>(r) * a.R0 * (a.L / 4);
-    const uint64_t *pos = reinterpret_cast<const uint64_t *>(a.st + 8 * a.S) + ubase;
-    const uint64_t p0 = pos[0];
-    int ok = (p0 & 3) == 0;
-    for (uint32_t k = threadIdx.x; k < a.units; k += blockDim.x) ok &= pos[k] == p0;
-    *blk0 = p0 >> 2;
-    return __syncthreads_and(ok) != 0;
-}
-
-// Whether every XS1024W instance with a unit in strip r has taken the same
-// number of steps: then *n0 is that count and *y_start the common Weyl word.
-__device__ inline bool strip_steps_uniform(const StripArgs &a, uint32_t r, uint64_t *n0, uint32_t *y_start) {
-    const uint64_t ubase = static_cast<uint64_t>(r) * a.R0 * (a.L / 8);
-    const uint64_t *N = reinterpret_cast<const uint64_t *>(a.st + 4 * a.S);
-    const uint64_t g0 = ubase >> 4, g1 = (ubase + a.units - 1) >> 4;
-    const uint64_t n = N[g0];
-    int ok = 1;
-    for (uint64_t g = g0 + threadIdx.x; g <= g1; g += blockDim.x) ok &= N[g] == n;
-    *n0 = n;
-    *y_start = *reinterpret_cast<const uint32_t *>(a.st + 4 * a.S + 8 * (a.S / 32)) + static_cast<uint32_t>(n) * kWeylC;
-    return __syncthreads_and(ok) != 0;
 }
 
 // EARLY: the strip's top row lies in slot 0 and its bottom row in slot SPT-1.
@@ -1324,6 +1051,54 @@ inline bool plan_early(int spt, uint32_t upr, uint32_t units, uint32_t nt) {
     return false;
 }
 
+// Workgroups of `fn` that fit on one CU with `threads` threads and `lds` bytes
+// of dynamic LDS, and the LDS allowed to it.  Asked of the runtime once per
+// device and shape: planning a lattice tries several kernels, and a lattice is
+// made more often than a shape is new.
+int blocks_per_cu(const void *fn, uint32_t threads, uint32_t lds) {
+    static std::mutex mu;
+    static std::map<std::tuple<int, const void *, uint32_t, uint32_t>, int> known;
+    static std::map<std::pair<int, const void *>, uint32_t> allowed;
+    int dev = 0;
+    if (!fn || hipGetDevice(&dev) != hipSuccess) return 0;
+    const auto key = std::make_tuple(dev, fn, threads, lds);
+    std::lock_guard<std::mutex> lk(mu);
+    if (auto it = known.find(key); it != known.end()) return it->second;
+    uint32_t &top = allowed[{dev, fn}];
+    if (lds > top) {
+        (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+        (void)hipGetLastError();
+        top = lds;
+    }
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, static_cast<int>(threads), lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    if (known.size() > 4096) known.clear();  // bounded: shapes of one process are few
+    known[key] = occ;
+    return occ;
+}
+
+// Kernel of a plan whose spins are bits.
+const void *bits_kernel_for(rngx_kind kind, uint32_t slots, bool hits, bool gang) {
+    const int n = static_cast<int>(slots);
+    switch (kind) {
+    case RNGX_LCG32:
+    case RNGX_LCG64:
+    case RNGX_MWC: return bits_kernel_lcg(kind, n, hits, gang);
+    case RNGX_LCG32_SUB:
+    case RNGX_LCG64_SUB:
+    case RNGX_MWC_DIFF: return bits_kernel_own(kind, n, hits, gang);
+    case RNGX_PHILOX4X32_10:
+    case RNGX_PHILOX4X32_7: return bits_kernel_philox(kind, n, hits, gang);
+    case RNGX_XORWOW:
+    case RNGX_XS1024W: return bits_kernel_xorshift(kind, n, hits, gang);
+    default: break;
+    }
+    return nullptr;
+}
+
 template <class Unit, bool MH>
 hipError_t run_passes(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t *tr, hipStream_t st, uint32_t hits) {
     constexpr int NB = Unit::kNB;
@@ -1345,15 +1120,14 @@ hipError_t run_passes(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
 template <class Unit, bool MH>
 hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t *tr, hipStream_t st, uint32_t hits) {
     const IsingPlan &pl = lat->plan;
-    const void *fn = strip_kernel_for<Unit, MH>(pl.spt, pl.early);
-    if (MH) {
+    const void *fn = pl.bits ? bits_kernel_for(lat->gen->kind, pl.bits_slots, MH, pl.nwg > 1)
+                             : strip_kernel_for<Unit, MH>(pl.spt, pl.early);
+    const dim3 block(pl.bits ? pl.bits_threads : pl.threads);
+    const uint32_t lds = pl.bits ? bits_lds_bytes(lat->gen->kind, pl.bits_slots) : pl.lds;
+    if (MH && !pl.bits) {
         // The plan was sized with the single-hit kernel: give this one the
         // same LDS and check that every strip can still be resident.
-        (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(pl.lds));
-        int occ = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, static_cast<int>(pl.threads), pl.lds) != hipSuccess ||
-            static_cast<uint64_t>(occ) * lat->gen->n_cu < pl.nwg) {
-            (void)hipGetLastError();
+        if (static_cast<uint64_t>(blocks_per_cu(fn, pl.threads, pl.lds)) * lat->gen->n_cu < pl.nwg) {
             return run_passes<Unit, MH>(lat, T4, T8, n, tr, st, hits);
         }
     }
@@ -1361,24 +1135,101 @@ hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
         hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<unsigned>((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
                            reinterpret_cast<uint32_t *>(tr), n);
     }
-    if (pl.nwg > 1 && lat->epoch + 2 * n + 2 >= (1ull << 31)) {  // restart the pass tags before they wrap
-        const uint64_t words = 2ull * pl.nwg * lat->L;              // halo size in uint32
+    if (pl.nwg > 1 && lat->epoch + 2 * n + 3 >= (1ull << 31)) {  // restart the pass tags before they wrap
+        const uint64_t words = halo_bytes(pl.nwg, lat->L) / 4;
         hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<unsigned>((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
                            reinterpret_cast<uint32_t *>(lat->d_halo), words);
         lat->epoch = 0;
     }
     StripArgs a{lat->d_spins, lat->gen->d_state, lat->gen->S, lat->L, pl.R, pl.nwg, pl.units, T4, T8, n,
-                tr, lat->d_halo, static_cast<uint32_t>(lat->epoch), lat->d_err, hits, pl.R};
+                tr, lat->d_halo, static_cast<uint32_t>(lat->epoch), lat->d_err, hits, pl.R, 0, 0, pl.VB};
     void *args[] = {&a};
     hipError_t e;
     if (pl.nwg == 1)
-        e = hipLaunchKernel(fn, dim3(1), dim3(pl.threads), args, pl.lds, st);
+        e = hipLaunchKernel(fn, dim3(1), block, args, lds, st);
     else
-        e = hipLaunchCooperativeKernel(fn, dim3(pl.nwg), dim3(pl.threads), args, pl.lds, st);
+        e = hipLaunchCooperativeKernel(fn, dim3(pl.nwg), block, args, lds, st);
     if (e != hipSuccess) return e;
-    lat->epoch += 2 * n;
+    lat->epoch += 2 * n + 1;  // one tag per pass, one for the state before
     return hipGetLastError();
 }
+
+// VALU instructions of one slot's draws in a colour pass, comparisons and
+// shifts into the outcome words included (counted in the compiled loops), and
+// of a pass beside its draws.
+int bits_slot_cost(rngx_kind kind) {
+    switch (kind) {
+    case RNGX_XS1024W: return 50;
+    case RNGX_PHILOX4X32_10: return 36;
+    case RNGX_PHILOX4X32_7: return 28;
+    case RNGX_XORWOW: return 24;
+    case RNGX_LCG64:
+    case RNGX_LCG64_SUB: return 18;
+    default: return 12;
+    }
+}
+constexpr int kBitsPassCost = 80;
+
+// Rows side by side (VB) and slots per thread of a strip of R rows whose
+// spins are bits; the strip's neighbours have R rows too, or fewer at the
+// lattice's end.  nt = VB L / NB threads hold units; XS1024W needs nt to be a
+// multiple of 16 (an instance's units on one 16-lane row), a lone strip VB to
+// divide R (its far rows are its own), strips of a lattice nt / (32 / NB)
+// tagged words in the L / 2 of their halo slot.  Of the shapes that fit, the
+// one with the fewest instructions on a SIMD per pass is taken: more threads
+// take fewer slots each, but every wave pays for the pass itself.  False where
+// none fits: the row is then too ragged for XS1024W (L / 8 threads and VB rows
+// do not meet in 16s within the workgroup) or takes more than 32 sites of a
+// colour per thread, and the strip keeps its spins as bytes.
+bool bits_shape(rngx_kind kind, uint32_t L, uint32_t R, uint32_t nwg, uint32_t NB, uint32_t max_threads,
+                uint32_t *VB_out, uint32_t *slots_out) {
+    static constexpr uint32_t kSlots[] = {1, 2, 4, 6, 8, 12, 16};
+    const uint32_t upr = L / NB, max_slots = 64 / NB;
+    uint32_t best = 0xFFFFFFFFu;
+    for (uint32_t VB = 1; VB <= R && VB * upr <= max_threads; ++VB) {
+        const uint32_t nt = VB * upr;
+        if (NB == 8 && nt % 16) continue;
+        if (nwg == 1 && R % VB) continue;
+        if (nwg > 1 && (nt + 32 / NB - 1) / (32 / NB) > L / 2) continue;
+        const uint32_t H = (R + VB - 1) / VB;
+        uint32_t slots = 0;
+        for (uint32_t s : kSlots)
+            if (s >= H && s <= max_slots) { slots = s; break; }
+        if (!slots) continue;
+        const uint32_t cost = (nt + 255) / 256 * (slots * bits_slot_cost(kind) + kBitsPassCost);
+        if (cost <= best) {
+            best = cost;
+            *VB_out = VB;
+            *slots_out = slots;
+        }
+    }
+    return best != 0xFFFFFFFFu;
+}
+
+// Whether the plan's strips can keep their spins as bits (both kernels with
+// every strip resident); fills the plan's shape.
+bool try_bits(uint32_t L, rngx_kind kind, uint32_t NB, int n_cu, IsingPlan *p) {
+    if (!bits_shape(kind, L, p->R, p->nwg, NB, kMaxThreads, &p->VB, &p->bits_slots)) return false;
+    p->bits_threads = (p->VB * (L / NB) + 63) / 64 * 64;
+    for (bool hits : {false, true}) {
+        const void *fn = bits_kernel_for(kind, p->bits_slots, hits, p->nwg > 1);
+        const uint32_t lds = bits_lds_bytes(kind, p->bits_slots);
+        if (static_cast<uint64_t>(blocks_per_cu(fn, p->bits_threads, lds)) * n_cu < p->nwg) return false;
+    }
+    return true;
+}
+
+template <class Unit> struct KindOf { static constexpr rngx_kind kind = static_cast<rngx_kind>(0); };
+template <> struct KindOf<SmallUnit<Lcg32>> { static constexpr rngx_kind kind = RNGX_LCG32; };
+template <> struct KindOf<SmallUnit<Lcg32Sub>> { static constexpr rngx_kind kind = RNGX_LCG32_SUB; };
+template <> struct KindOf<SmallUnit<Lcg64>> { static constexpr rngx_kind kind = RNGX_LCG64; };
+template <> struct KindOf<SmallUnit<Lcg64Sub>> { static constexpr rngx_kind kind = RNGX_LCG64_SUB; };
+template <> struct KindOf<SmallUnit<Mwc>> { static constexpr rngx_kind kind = RNGX_MWC; };
+template <> struct KindOf<SmallUnit<MwcDiff>> { static constexpr rngx_kind kind = RNGX_MWC_DIFF; };
+template <> struct KindOf<SmallUnit<Xorwow>> { static constexpr rngx_kind kind = RNGX_XORWOW; };
+template <> struct KindOf<PhiloxUnit> { static constexpr rngx_kind kind = RNGX_PHILOX4X32_10; };
+template <> struct KindOf<PhiloxUnit7> { static constexpr rngx_kind kind = RNGX_PHILOX4X32_7; };
+template <> struct KindOf<XsUnit> { static constexpr rngx_kind kind = RNGX_XS1024W; };
 
 // Try one decomposition into nwg strips; fills *out if it fits on chip.
 template <class Unit>
@@ -1410,16 +1261,12 @@ bool try_strips(uint32_t L, uint32_t nwg, int max_spt, int n_cu, IsingPlan *out)
         if (place_lds_for<Unit>(spt)) b += 4ull * spt * threads;
         if (b > kLdsMax) return false;
         const void *fn = strip_kernel_for<Unit>(spt, early);
-        (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(b));
-        (void)hipGetLastError();
-        int occ = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, static_cast<int>(threads), b) != hipSuccess ||
-            occ < 1) {
-            (void)hipGetLastError();
-            return false;
-        }
+        const int occ = blocks_per_cu(fn, threads, static_cast<uint32_t>(b));
+        if (occ < 1) return false;
         if (static_cast<uint64_t>(occ) * n_cu >= nwg) {
-            *out = IsingPlan{true, R, nwg, units, static_cast<uint32_t>(spt), threads, static_cast<uint32_t>(b), early};
+            *out = IsingPlan{true, R, nwg, units, static_cast<uint32_t>(spt), threads, static_cast<uint32_t>(b), early,
+                             false, 0, 0, 0};
+            out->bits = try_bits(L, KindOf<Unit>::kind, NB, n_cu, out);
             return true;
         }
     }

@@ -76,7 +76,16 @@ struct IsingPlan {
     uint32_t threads;  // threads per workgroup
     uint32_t lds;      // dynamic LDS bytes per workgroup
     bool early;        // top and bottom rows in the first and last unit slots
+    // spins as bits (bits = true: the sweeps run k_ising_bits, else k_ising_strip)
+    bool bits;
+    uint32_t VB;            // rows side by side in a workgroup
+    uint32_t bits_slots;    // slots per thread of the kernel
+    uint32_t bits_threads;  // threads per workgroup
 };
+
+// Halo of a lattice cut into nwg strips: two slots of at most L / 2 64-bit
+// tagged words a strip.
+inline uint64_t halo_bytes(uint32_t nwg, uint32_t L) { return 8ull * nwg * L; }
 
 struct Ising {
     uint64_t magic;
@@ -85,7 +94,7 @@ struct Ising {
     int8_t *d_spins;
     Gen *gen;
     IsingPlan plan;
-    uint64_t *d_halo;    // strips: 2 slots x nwg x 2 rows x L/4 tagged words (4 spins | pass tag << 32)
+    uint64_t *d_halo;    // strips: halo_bytes of tagged words (spins | pass tag << 32)
     uint32_t halo_nwg;   // strips the halo allocation is sized for
     uint32_t *d_err;     // strips: set if a neighbour wait gave up
     int32_t *d_partial;  // per-pass path: per-block energy partials
@@ -187,6 +196,12 @@ hipError_t launch_hot_start(Ising *lat, uint64_t seed, hipStream_t st);
 hipError_t launch_ising(Ising *lat, double beta, uint64_t n_sweeps, int32_t *d_trace, hipStream_t st,
                         uint32_t hits = 1);  // hits: Metropolis updates per visited site
 hipError_t launch_zero(uint32_t *p, uint64_t n, hipStream_t st);
+// Kernels of strips with spins as bits, for `slots` slots per thread; gang:
+// for several strips.
+const void *bits_kernel_lcg(rngx_kind kind, int slots, bool hits, bool gang);
+const void *bits_kernel_own(rngx_kind kind, int slots, bool hits, bool gang);
+const void *bits_kernel_philox(rngx_kind kind, int slots, bool hits, bool gang);
+const void *bits_kernel_xorshift(rngx_kind kind, int slots, bool hits, bool gang);
 bool ising_plan(uint32_t L, rngx_kind kind, int n_cu, IsingPlan *out);
 int ising_plan_list(uint32_t L, rngx_kind kind, int n_cu, IsingPlan *out, int max);  // strip candidates
 // Plans b (shape b->shape) from b->lats, b->betas, b->traces and `sweeps`
