@@ -28,17 +28,16 @@
 #include <map>
 #include <mutex>
 #include <numeric>
+#include <queue>
 #include <tuple>
 #include <type_traits>
 #include <vector>
 
-#include "ising_device.h"
+#include "ising_memory.h"
 
 namespace rngx {
 
 namespace {
-
-constexpr uint64_t kOnes8 = 0x0101010101010101ull;
 
 __global__ __launch_bounds__(kBlock) void k_hot_start(int8_t *spins, uint64_t n_words, uint64_t seed) {
     const uint64_t q = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -59,71 +58,7 @@ __global__ __launch_bounds__(kBlock) void k_zero_u32(uint32_t *p, uint64_t n) {
     if (i < n) p[i] = 0;
 }
 
-// Bytewise count (0..4) of neighbours that differ from each site of an
-// NB-site run w; up/dn are the runs above and below, lb/rb the spins left of
-// byte 0 and right of byte NB-1.
-template <int NB>
-__device__ __forceinline__ uint64_t mismatches(uint64_t w, uint64_t up, uint64_t dn, uint32_t lb, uint32_t rb) {
-    constexpr uint64_t M = NB == 8 ? kOnes8 : 0x01010101ull;
-    const uint64_t nw = (w >> 1) & M, nu = (up >> 1) & M, nd = (dn >> 1) & M;
-    const uint64_t nl = ((nw << 8) | ((lb >> 1) & 1u)) & M;
-    const uint64_t nr = (nw >> 8) | (static_cast<uint64_t>((rb >> 1) & 1u) << (8 * (NB - 1)));
-    return (nu ^ nw) + (nd ^ nw) + (nl ^ nw) + (nr ^ nw);
-}
-
-// Metropolis decision for byte i; returns s_i h_i after the update.  Written
-// without branches: the flip is a masked xor and the result a select.
-__device__ __forceinline__ int metropolis(uint64_t &w, uint64_t m, int i, uint32_t r, uint64_t T4, uint64_t T8) {
-    const uint32_t mi = static_cast<uint32_t>(m >> (8 * i)) & 0xFFu;
-    const uint64_t thr = mi == 1 ? T4 : T8;
-    const uint32_t acc = static_cast<uint32_t>(mi >= 2) | static_cast<uint32_t>(static_cast<uint64_t>(r) < thr);
-    w ^= static_cast<uint64_t>(acc * 0xFEu) << (8 * i);
-    const int e = 2 * static_cast<int>(mi) - 4;
-    return acc ? e : -e;
-}
-
-// One Metropolis update of a site with mi (0..4) differing neighbours and
-// draw r (multi-hit updates: the site's neighbours stay fixed between its
-// hits); a taken flip turns mi into 4 - mi and toggles `flip`.
-__device__ __forceinline__ void hit_mem(uint32_t &mi, uint32_t &flip, uint32_t r, uint64_t T4, uint64_t T8) {
-    const uint64_t thr = mi == 1 ? T4 : T8;
-    const bool acc = (mi >= 2) | (static_cast<uint64_t>(r) < thr);
-    mi = acc ? 4 - mi : mi;
-    flip ^= acc ? 1u : 0u;
-}
-
-template <int NB>
-__device__ __forceinline__ uint64_t lds_run(const uint8_t *p) {
-    if constexpr (NB == 8) return *reinterpret_cast<const uint64_t *>(p);
-    else return *reinterpret_cast<const uint32_t *>(p);
-}
-template <int NB>
-__device__ __forceinline__ void lds_put(uint8_t *p, uint64_t w) {
-    if constexpr (NB == 8) *reinterpret_cast<uint64_t *>(p) = w;
-    else *reinterpret_cast<uint32_t *>(p) = static_cast<uint32_t>(w);
-}
-
 // ---------------------------------------------------------------- strips
-// A batch replica runs in one of three modes: in memory by one workgroup
-// (kReplicaMemory), on chip by one workgroup (kReplicaOnChip, R = L), or as
-// a gang of nwg strip workgroups of R rows each (kReplicaStrips) that
-// exchange tagged halo words like the strips of one lattice.
-constexpr uint32_t kReplicaMemory = 0, kReplicaOnChip = 1, kReplicaStrips = 2;
-struct ReplicaDesc {
-    int8_t *spins;
-    uint8_t *st;
-    uint64_t S;
-    uint32_t L, mode;
-    uint64_t T4, T8, n_sweeps;
-    int32_t *trace;   // may be null
-    uint32_t R, nwg, units;  // strips: rows and units per strip, strip count
-    uint64_t *halo;   // strips: 2 slots x nwg x 2 rows x L/4 tagged words
-    uint32_t *err;    // the lattice's error word (a strip gave up waiting)
-    uint32_t R_last;  // strips: rows of the last strip (1..R; the others have R)
-    uint32_t *gang;   // strips: arrival counter of the gang's workgroups (zeroed before each run)
-    uint64_t start_ticks;  // strips: wall-clock ticks a gang member waits for the others to start
-};
-
 // Two rows of L bytes (src0 -> dst0, src1 -> dst1) by the whole block: all
 // loads are issued before the first LDS write, one round trip in all.
 __device__ __forceinline__ void copy_rows(uint8_t *dst0, const uint8_t *src0, uint8_t *dst1, const uint8_t *src1,
@@ -135,20 +70,6 @@ __device__ __forceinline__ void copy_rows(uint8_t *dst0, const uint8_t *src0, ui
         const uint4 v = *reinterpret_cast<const uint4 *>((second ? src1 : src0) + o);
         *reinterpret_cast<uint4 *>((second ? dst1 : dst0) + o) = v;
     }
-}
-
-// Sum of v over the block (result valid in thread 0).
-__device__ __forceinline__ int block_sum(int v, int *scratch) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    const uint32_t w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-    if ((threadIdx.x & 63) == 0) scratch[w] = v;
-    __syncthreads();
-    int s = 0;
-    if (threadIdx.x == 0)
-        for (uint32_t i = 0; i < nw; ++i) s += scratch[i];
-    __syncthreads();
-    return s;
 }
 
 // ---------------------------------------------------------------- on-chip update
@@ -651,81 +572,6 @@ struct PassArgs {
     uint32_t hits;     // multi-hit kernels only
 };
 
-// Update unit k of colour c with spins and state in global memory; returns
-// the sum of s*h over the updated sites.  A unit reads only other-colour
-// bytes of its neighbour runs, which no thread writes during the pass.
-template <class Unit, bool MH = false>
-__device__ __forceinline__ int unit_in_memory_with(Unit &u, uint8_t *sp, uint8_t *st, uint64_t S, uint32_t L,
-                                                   uint64_t k, int c, uint64_t T4, uint64_t T8, uint32_t hits);
-
-template <class Unit, bool MH = false>
-__device__ __forceinline__ int unit_in_memory(uint8_t *sp, uint8_t *st, uint64_t S, uint32_t L, uint64_t k, int c,
-                                              uint64_t T4, uint64_t T8, uint32_t hits = 1) {
-    Unit u;
-    u.load(st, S, k);
-    return unit_in_memory_with<Unit, MH>(u, sp, st, S, L, k, c, T4, T8, hits);
-}
-
-// The update with the unit's generator already loaded (it stores it back).
-template <class Unit, bool MH>
-__device__ __forceinline__ int unit_in_memory_with(Unit &u, uint8_t *sp, uint8_t *st, uint64_t S, uint32_t L,
-                                                   uint64_t k, int c, uint64_t T4, uint64_t T8, uint32_t hits) {
-    constexpr int NB = Unit::kNB;
-    // L <= 16384: unit indices and site offsets fit 32 bits (no 64-bit division)
-    const uint32_t upr = L / NB, k32 = static_cast<uint32_t>(k);
-    const uint32_t y = k32 / upr;
-    const uint32_t x0 = (k32 - y * upr) * NB;
-    const uint32_t row = y * L, up_row = (y == 0 ? L - 1 : y - 1) * L;
-    const uint32_t dn_row = (y == L - 1 ? 0 : y + 1) * L;
-    uint64_t w = lds_run<NB>(sp + row + x0);
-    const uint64_t upw = lds_run<NB>(sp + up_row + x0), dnw = lds_run<NB>(sp + dn_row + x0);
-    const uint32_t lb = sp[row + (x0 == 0 ? L - 1 : x0 - 1)];
-    const uint32_t rb = sp[row + (x0 + NB == L ? 0 : x0 + NB)];
-    const uint64_t m = mismatches<NB>(w, upw, dnw, lb, rb);
-    const int p = static_cast<int>((c + y) & 1);
-    int sh = 0;
-    if constexpr (MH) {
-        // byte p + 2h is site h; the same draw order as the on-chip update
-        uint32_t mi[NB / 2], fl[NB / 2];
-#pragma unroll
-        for (int h = 0; h < NB / 2; ++h) {
-            mi[h] = static_cast<uint32_t>(m >> (8 * (p + 2 * h))) & 0xFFu;
-            fl[h] = 0;
-        }
-        if constexpr (NB == 4) {
-            u.draws2(hits, [&](uint32_t r) { hit_mem(mi[0], fl[0], r, T4, T8); },
-                     [&](uint32_t r) { hit_mem(mi[1], fl[1], r, T4, T8); });
-        } else {
-            for (uint32_t i = 0; i < hits; ++i) {
-                uint32_t ra, rb;
-                u.pair(ra, rb);
-                hit_mem(mi[0], fl[0], ra, T4, T8);
-                hit_mem(mi[2], fl[2], rb, T4, T8);
-            }
-            for (uint32_t i = 0; i < hits; ++i) {
-                uint32_t ra, rb;
-                u.pair(ra, rb);
-                hit_mem(mi[1], fl[1], ra, T4, T8);
-                hit_mem(mi[3], fl[3], rb, T4, T8);
-            }
-        }
-        u.store(st, S, k, 2 * hits);
-#pragma unroll
-        for (int h = 0; h < NB / 2; ++h) {
-            w ^= static_cast<uint64_t>(fl[h] * 0xFEu) << (8 * (p + 2 * h));
-            sh += 4 - 2 * static_cast<int>(mi[h]);
-        }
-    } else {
-        uint32_t rr[NB / 2];
-        u.draw(rr);
-        u.store(st, S, k, 2);
-#pragma unroll
-        for (int h = 0; h < NB / 2; ++h) sh += metropolis(w, m, p + 2 * h, rr[h], T4, T8);
-    }
-    lds_put<NB>(sp + row + x0, w);
-    return sh;
-}
-
 template <class Unit, bool MH>
 __global__ __launch_bounds__(kBlock) void k_ising_pass(PassArgs a, uint64_t n_units) {
     const uint64_t k = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -900,50 +746,6 @@ __global__ __launch_bounds__(1024) void k_ising_lfg_one(PassArgs a, uint64_t n_s
 // decreasing work) and runs all its sweeps alone -- on chip when the
 // lattice fits, otherwise streaming it through memory -- so no workgroup
 // ever waits for another.
-template <class Unit>
-__device__ void replica_in_memory(const ReplicaDesc &d, int *red) {
-    constexpr int NB = Unit::kNB;
-    const uint64_t n_units = static_cast<uint64_t>(d.L) * d.L / NB;
-    uint8_t *sp = reinterpret_cast<uint8_t *>(d.spins);
-    for (uint64_t sweep = 0; sweep < d.n_sweeps; ++sweep) {
-        for (int c = 0; c < 2; ++c) {
-            int sh = 0;
-            // XS1024W: n_units and blockDim are multiples of 16, rows stay whole
-            for (uint64_t k = threadIdx.x; k < n_units; k += blockDim.x)
-                sh += unit_in_memory<Unit>(sp, d.st, d.S, d.L, k, c, d.T4, d.T8);
-            __syncthreads();
-            if (c == 1 && d.trace) {
-                const int tot = block_sum(sh, red);
-                if (threadIdx.x == 0) d.trace[sweep] = -tot;
-            }
-        }
-    }
-}
-
-// A gang's strips wait on each other every pass, so none of them may start
-// its sweeps before all of them run.  Items are claimed one at a time, so the
-// first strips of a gang can be claimed long before the last ones (the other
-// workgroups may be busy with long independent items): each member checks in
-// and waits here, bounded by wall-clock time rather than a poll count, until
-// all nwg have arrived.  They always do, as every other claimed item finishes
-// on its own and frees its workgroup for the gang's next strip; if the bound
-// is reached anyway (the device held by other work for that long), the
-// lattice is marked invalid and its strips end quickly.
-__device__ void gang_start(const ReplicaDesc &d) {
-    if (threadIdx.x == 0) {
-        __hip_atomic_fetch_add(d.gang, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint64_t t0 = static_cast<uint64_t>(wall_clock64());
-        while (__hip_atomic_load(d.gang, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < d.nwg) {
-            if (static_cast<uint64_t>(wall_clock64()) - t0 > d.start_ticks || __hip_atomic_load(d.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                __hip_atomic_fetch_or(d.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(127);
-        }
-    }
-    __syncthreads();
-}
-
 // Units per thread of an on-chip replica (at most 16384 four-site or 8192
 // eight-site units, i.e. L <= 256, with 1024 threads).
 template <class Unit>
@@ -994,7 +796,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_prologue(const ReplicaDesc *re
     if (blockIdx.x == 0 && threadIdx.x == 0) *next = 0;
     if (d.mode != kReplicaStrips) return;
     uint32_t *h = reinterpret_cast<uint32_t *>(d.halo);
-    const uint64_t words = 2ull * d.nwg * d.L;
+    const uint64_t words = 2ull * d.nwg * d.L;  // halo_bytes
     for (uint64_t i = threadIdx.x; i < words; i += kBlock) h[i] = 0;
     if (threadIdx.x == 0) *d.gang = 0;
     if (d.trace)
@@ -1123,7 +925,7 @@ hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
     const void *fn = pl.bits ? bits_kernel_for(lat->gen->kind, pl.bits_slots, MH, pl.nwg > 1)
                              : strip_kernel_for<Unit, MH>(pl.spt, pl.early);
     const dim3 block(pl.bits ? pl.bits_threads : pl.threads);
-    const uint32_t lds = pl.bits ? bits_lds_bytes(lat->gen->kind, pl.bits_slots) : pl.lds;
+    const uint32_t lds = pl.bits ? bits_lds_bytes(lat->gen->kind, pl.bits_threads, pl.bits_slots) : pl.lds;
     if (MH && !pl.bits) {
         // The plan was sized with the single-hit kernel: give this one the
         // same LDS and check that every strip can still be resident.
@@ -1182,9 +984,9 @@ constexpr int kBitsPassCost = 80;
 // do not meet in 16s within the workgroup) or takes more than 32 sites of a
 // colour per thread, and the strip keeps its spins as bytes.
 bool bits_shape(rngx_kind kind, uint32_t L, uint32_t R, uint32_t nwg, uint32_t NB, uint32_t max_threads,
-                uint32_t *VB_out, uint32_t *slots_out) {
-    static constexpr uint32_t kSlots[] = {1, 2, 4, 6, 8, 12, 16};
-    const uint32_t upr = L / NB, max_slots = 64 / NB;
+                uint32_t max_slots, const std::vector<uint32_t> &slot_list, uint32_t *VB_out, uint32_t *slots_out,
+                uint32_t *cost_out = nullptr) {
+    const uint32_t upr = L / NB;
     uint32_t best = 0xFFFFFFFFu;
     for (uint32_t VB = 1; VB <= R && VB * upr <= max_threads; ++VB) {
         const uint32_t nt = VB * upr;
@@ -1193,7 +995,7 @@ bool bits_shape(rngx_kind kind, uint32_t L, uint32_t R, uint32_t nwg, uint32_t N
         if (nwg > 1 && (nt + 32 / NB - 1) / (32 / NB) > L / 2) continue;
         const uint32_t H = (R + VB - 1) / VB;
         uint32_t slots = 0;
-        for (uint32_t s : kSlots)
+        for (uint32_t s : slot_list)
             if (s >= H && s <= max_slots) { slots = s; break; }
         if (!slots) continue;
         const uint32_t cost = (nt + 255) / 256 * (slots * bits_slot_cost(kind) + kBitsPassCost);
@@ -1203,17 +1005,19 @@ bool bits_shape(rngx_kind kind, uint32_t L, uint32_t R, uint32_t nwg, uint32_t N
             *slots_out = slots;
         }
     }
+    if (cost_out) *cost_out = best;
     return best != 0xFFFFFFFFu;
 }
 
 // Whether the plan's strips can keep their spins as bits (both kernels with
 // every strip resident); fills the plan's shape.
 bool try_bits(uint32_t L, rngx_kind kind, uint32_t NB, int n_cu, IsingPlan *p) {
-    if (!bits_shape(kind, L, p->R, p->nwg, NB, kMaxThreads, &p->VB, &p->bits_slots)) return false;
+    static const std::vector<uint32_t> kSlots = {1, 2, 4, 6, 8, 12, 16};
+    if (!bits_shape(kind, L, p->R, p->nwg, NB, kMaxThreads, 64 / NB, kSlots, &p->VB, &p->bits_slots)) return false;
     p->bits_threads = (p->VB * (L / NB) + 63) / 64 * 64;
     for (bool hits : {false, true}) {
         const void *fn = bits_kernel_for(kind, p->bits_slots, hits, p->nwg > 1);
-        const uint32_t lds = bits_lds_bytes(kind, p->bits_slots);
+        const uint32_t lds = bits_lds_bytes(kind, p->bits_threads, p->bits_slots);
         if (static_cast<uint64_t>(blocks_per_cu(fn, p->bits_threads, lds)) * n_cu < p->nwg) return false;
     }
     return true;
@@ -1327,6 +1131,103 @@ const void *batch_kernel_for(rngx_kind kind, uint32_t threads) {
     return nullptr;
 }
 
+const void *batch_bits_kernel_for(rngx_kind kind, uint32_t threads) {
+    switch (kind) {
+    case RNGX_LCG32:
+    case RNGX_LCG64:
+    case RNGX_MWC: return batch_bits_kernel_lcg(kind, threads);
+    case RNGX_LCG32_SUB:
+    case RNGX_LCG64_SUB:
+    case RNGX_MWC_DIFF: return batch_bits_kernel_own(kind, threads);
+    case RNGX_PHILOX4X32_10:
+    case RNGX_PHILOX4X32_7: return batch_bits_kernel_philox(kind, threads);
+    case RNGX_XORWOW:
+    case RNGX_XS1024W: return batch_bits_kernel_xorshift(kind, threads);
+    default: break;
+    }
+    return nullptr;
+}
+
+const void *batch_kernel_for(const IsingBatch *b) {
+    const uint32_t threads = kBatchShape[b->shape].threads;
+    return b->bits ? batch_bits_kernel_for(b->kind, threads) : batch_kernel_for(b->kind, threads);
+}
+
+// A replica's tiling: the fewest strips (one if possible) of at most
+// max_units units that `fits` takes: strips of R rows and a last one of R_last
+// = L - (nwg - 1) R rows (2 <= R_last <= R), so that L need not be a multiple
+// of R.  XS1024W strips hold whole instances (128 sites), so R is a multiple
+// of g = 128 / gcd(L, 128) (L is a multiple of 16, hence of g).
+template <class Fits>
+bool tile_replica(uint32_t L, uint32_t nb, uint64_t max_units, ReplicaDesc *d, Fits &&fits) {
+    const uint32_t g = nb == 8 ? 128u / std::gcd(L, 128u) : 1u;
+    for (uint32_t want = 1; want <= kMaxGang; ++want) {
+        uint32_t R = (L + want - 1) / want;
+        R = std::min((R + g - 1) / g * g, L);
+        const uint32_t nwg = (L + R - 1) / R;
+        const uint32_t R_last = L - (nwg - 1) * R;
+        if (nwg > 1 && R_last < 2) continue;  // a strip's top and bottom rows are distinct
+        const uint64_t units = static_cast<uint64_t>(R) * L / nb;
+        if (units > max_units) continue;
+        if (nb == 8 && ((static_cast<uint64_t>(R) * L) % 128 || (static_cast<uint64_t>(R_last) * L) % 128)) continue;
+        d->mode = nwg == 1 ? kReplicaOnChip : kReplicaStrips;
+        d->R = R;
+        d->R_last = R_last;
+        d->nwg = nwg;
+        d->units = static_cast<uint32_t>(units);
+        if (fits(d)) return true;
+    }
+    d->mode = kReplicaMemory;
+    d->R = d->R_last = d->nwg = d->units = 0;
+    return false;
+}
+
+// Tiles every replica for strips with spins as bits and at most max_units
+// units each, into `reps`; false if one that bytes could hold does not fit so.
+// *span: the run's length in VALU instructions per SIMD with `machines`
+// workgroups at once, items taken in order of decreasing work, a gang's
+// together (a gang's pass takes no less than kGangPass, the exchange).
+bool tile_bits(rngx_kind kind, const BatchShape &sh, uint32_t nb, uint64_t max_units, uint32_t machines,
+               std::vector<ReplicaDesc> *reps, double *span) {
+    constexpr uint32_t kGangPass = 600;
+    const uint32_t most = sh.sites_per_thread / nb, top = 64 / nb;
+    const std::vector<uint32_t> slots = {top / 4, top / 2, top};  // the batch kernel's bodies
+    std::vector<std::pair<double, uint32_t>> work;                // (time, workgroups)
+    double alone = 0;
+    for (ReplicaDesc &d : *reps) {
+        uint32_t cost = 0;
+        const bool on_chip = tile_replica(d.L, nb, max_units, &d, [&](ReplicaDesc *x) {
+            return bits_shape(kind, x->L, x->R, x->nwg, nb, sh.threads, most, slots, &x->VB, &x->slots, &cost);
+        });
+        if (!on_chip) {
+            ReplicaDesc y = d;
+            if (tile_replica(d.L, nb, static_cast<uint64_t>(sh.sites_per_thread) * sh.threads / nb, &y, [&](ReplicaDesc *x) {
+                    return strip_lds_bytes(x->L, x->R) <= sh.lds_cap;
+                }))
+                return false;
+            alone += static_cast<double>(d.L) * d.L * d.n_sweeps;  // streams through memory, the same in every tiling
+            continue;
+        }
+        if (d.nwg > 1) cost = std::max(cost, kGangPass);
+        work.emplace_back(static_cast<double>(cost) * d.n_sweeps, d.nwg);
+    }
+    std::stable_sort(work.begin(), work.end(), [](auto &x, auto &y) { return x.first > y.first; });
+    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+    for (uint32_t i = 0; i < machines; ++i) free_at.push(0);
+    double end = 0;
+    for (auto &w : work) {
+        double start = 0;
+        for (uint32_t i = 0; i < w.second; ++i) {  // a gang starts when its last member does
+            start = free_at.top();
+            free_at.pop();
+        }
+        for (uint32_t i = 0; i < w.second; ++i) free_at.push(start + w.first);
+        end = std::max(end, start + w.first);
+    }
+    *span = end + alone;
+    return true;
+}
+
 uint64_t threshold(double beta, int dE) {
     return static_cast<uint64_t>(std::floor(std::exp(-beta * dE) * 4294967296.0));
 }
@@ -1359,41 +1260,46 @@ hipError_t batch_prepare(IsingBatch *b, const uint64_t *sweeps, bool with_traces
     const uint32_t nb = b->kind == RNGX_XS1024W ? 8 : 4;
     const uint64_t max_units = static_cast<uint64_t>(sh.sites_per_thread) * sh.threads / nb;
     std::vector<ReplicaDesc> reps(n);
-    uint32_t lds = 80;
-    uint64_t halo_bytes = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const Ising *l = b->lats[i];
-        const uint32_t L = l->L;
         int32_t *tr = with_traces ? b->traces[i] : nullptr;
-        ReplicaDesc d{l->d_spins, l->gen->d_state, l->gen->S, L, kReplicaMemory, threshold(b->betas[i], 4),
-                      threshold(b->betas[i], 8), sweeps[i], tr, 0, 0, 0, nullptr, l->d_err};
-        // Fewest strips (one if possible) that fit the workgroup's LDS and
-        // unit slots: strips of R rows and a last one of R_last = L - (nwg-1) R
-        // rows (2 <= R_last <= R), so that L need not be a multiple of R.
-        // XS1024W strips hold whole instances (128 sites), so R is a multiple
-        // of g = 128 / gcd(L, 128) (L is a multiple of 16, hence of g).
-        const uint32_t g = nb == 8 ? 128u / std::gcd(L, 128u) : 1u;
-        for (uint32_t want = 1; want <= kMaxGang; ++want) {
-            uint32_t R = (L + want - 1) / want;
-            R = std::min((R + g - 1) / g * g, L);
-            const uint32_t nwg = (L + R - 1) / R;
-            const uint32_t R_last = L - (nwg - 1) * R;
-            if (nwg > 1 && R_last < 2) continue;  // a strip's top and bottom rows are distinct
-            const uint64_t units = static_cast<uint64_t>(R) * L / nb;
-            if (units > max_units || strip_lds_bytes(L, R) > sh.lds_cap) continue;
-            if (nb == 8 && ((static_cast<uint64_t>(R) * L) % 128 || (static_cast<uint64_t>(R_last) * L) % 128))
-                continue;
-            d.mode = nwg == 1 ? kReplicaOnChip : kReplicaStrips;
-            d.R = R;
-            d.R_last = R_last;
-            d.nwg = nwg;
-            d.units = static_cast<uint32_t>(units);
-            lds = std::max<uint32_t>(lds, static_cast<uint32_t>(strip_lds_bytes(L, R)));
-            if (nwg > 1) halo_bytes += 8ull * nwg * L + kGangWordBytes;
-            break;
-        }
-        reps[i] = d;
+        reps[i] = ReplicaDesc{l->d_spins, l->gen->d_state, l->gen->S, l->L, kReplicaMemory, threshold(b->betas[i], 4),
+                              threshold(b->betas[i], 8), sweeps[i], tr, 0, 0, 0, nullptr, l->d_err};
     }
+    // Spins as bits if every replica's strips allow it, the strips at most as
+    // large as the shape lets them be and, where smaller ones spread a short
+    // list of items more evenly over the device, of the size that ends first.
+    b->bits = false;
+    uint32_t lds = bits_lds_bytes(b->kind, sh.threads, 64 / nb);
+    const void *bits_fn = batch_bits_kernel_for(b->kind, sh.threads);
+    const uint32_t bits_machines = static_cast<uint32_t>(blocks_per_cu(bits_fn, sh.threads, lds)) * std::max(b->n_cu, 1);
+    if (bits_machines >= 2 * kMaxGang) {
+        double best = 0;
+        std::vector<ReplicaDesc> tiled;
+        for (uint32_t part : {8, 6, 4, 3, 2}) {  // eighths of the largest strip
+            std::vector<ReplicaDesc> r = reps;
+            double span = 0;
+            if (!tile_bits(b->kind, sh, nb, max_units * part / 8, bits_machines, &r, &span)) {
+                if (part == 8) break;
+                continue;
+            }
+            if (!b->bits || span < 0.98 * best) {
+                b->bits = true;
+                best = span;
+                tiled = std::move(r);
+            }
+        }
+        if (b->bits) reps = std::move(tiled);
+    }
+    if (!b->bits) {
+        lds = 80;
+        for (ReplicaDesc &d : reps)
+            if (tile_replica(d.L, nb, max_units, &d, [&](ReplicaDesc *x) { return strip_lds_bytes(x->L, x->R) <= sh.lds_cap; }))
+                lds = std::max<uint32_t>(lds, static_cast<uint32_t>(strip_lds_bytes(d.L, d.R)));
+    }
+    uint64_t halo_bytes_all = 0;
+    for (const ReplicaDesc &d : reps)
+        if (d.mode == kReplicaStrips) halo_bytes_all += halo_bytes(d.nwg, d.L) + kGangWordBytes;
     // items: replicas by decreasing work per item, each gang's strips together
     std::vector<uint32_t> order(n);
     for (uint32_t i = 0; i < n; ++i) order[i] = i;
@@ -1404,20 +1310,11 @@ hipError_t batch_prepare(IsingBatch *b, const uint64_t *sweeps, bool with_traces
     std::vector<uint2> items;
     for (uint32_t x : order)
         for (uint32_t j = 0; j < std::max<uint32_t>(reps[x].nwg, 1); ++j) items.push_back(make_uint2(x, j));
-    const void *fn = batch_kernel_for(b->kind, sh.threads);
-    // the largest strip LDS of any shape, so that batches planned with other
-    // shapes keep launching
-    uint32_t lds_top = 0;
-    for (const BatchShape &x : kBatchShape) lds_top = std::max(lds_top, x.lds_cap);
-    (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_top));
-    (void)hipGetLastError();
-    int occ = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, sh.threads, lds);
-    if (e != hipSuccess) return e;
-    if (occ < 1) return hipErrorOutOfMemory;
-    const uint32_t resident = static_cast<uint32_t>(occ * std::max(b->n_cu, 1));
+    const void *fn = batch_kernel_for(b);
+    const uint32_t resident = static_cast<uint32_t>(blocks_per_cu(fn, sh.threads, lds) * std::max(b->n_cu, 1));
+    if (resident == 0) return hipErrorOutOfMemory;
     if (resident < 2 * kMaxGang) {  // too few workgroups to run gangs safely: strips go to memory
-        halo_bytes = 0;
+        halo_bytes_all = 0;
         for (auto &d : reps)
             if (d.mode == kReplicaStrips) d = ReplicaDesc{d.spins, d.st, d.S, d.L, kReplicaMemory, d.T4, d.T8,
                                                           d.n_sweeps, d.trace, 0, 0, 0, nullptr, d.err};
@@ -1425,17 +1322,18 @@ hipError_t batch_prepare(IsingBatch *b, const uint64_t *sweeps, bool with_traces
         for (uint32_t x : order) items.push_back(make_uint2(x, 0));
     }
     int clock_khz = 0;  // wall_clock64() rate
+    hipError_t e;
     if ((e = hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, b->device)) != hipSuccess) return e;
     const uint64_t start_ticks = static_cast<uint64_t>(kGangStartSeconds * 1e3 * std::max(clock_khz, 1));
-    if (halo_bytes) {
-        if ((e = hipMalloc(&b->d_halo, halo_bytes)) != hipSuccess) return e;
+    if (halo_bytes_all) {
+        if ((e = hipMalloc(&b->d_halo, halo_bytes_all)) != hipSuccess) return e;
         uint64_t off = 0;
         for (auto &d : reps)
             if (d.mode == kReplicaStrips) {
                 d.halo = reinterpret_cast<uint64_t *>(reinterpret_cast<uint8_t *>(b->d_halo) + off);
-                d.gang = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(b->d_halo) + off + 8ull * d.nwg * d.L);
+                d.gang = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(b->d_halo) + off + halo_bytes(d.nwg, d.L));
                 d.start_ticks = start_ticks;
-                off += 8ull * d.nwg * d.L + kGangWordBytes;
+                off += halo_bytes(d.nwg, d.L) + kGangWordBytes;
             }
     }
     if ((e = hipMalloc(&b->d_reps, sizeof(ReplicaDesc) * n)) != hipSuccess) return e;
@@ -1447,7 +1345,7 @@ hipError_t batch_prepare(IsingBatch *b, const uint64_t *sweeps, bool with_traces
     b->lds = lds;
     b->n_items = static_cast<uint32_t>(items.size());
     b->resident = resident;
-    b->gangs = halo_bytes != 0;
+    b->gangs = halo_bytes_all != 0;
     b->grid = std::min<uint32_t>(b->n_items, resident);
     return hipSuccess;
 }
@@ -1458,7 +1356,7 @@ hipError_t launch_batch(IsingBatch *b, hipStream_t st) {
     const auto *reps = static_cast<const ReplicaDesc *>(b->d_reps);
     const auto *items = static_cast<const uint2 *>(b->d_items);
     hipLaunchKernelGGL(k_batch_prologue, dim3(b->n), dim3(kBlock), 0, st, reps, b->d_next);
-    const void *fn = batch_kernel_for(b->kind, kBatchShape[b->shape].threads);
+    const void *fn = batch_kernel_for(b);
     if (!fn) return hipErrorInvalidValue;
     uint32_t n_items = b->n_items;
     uint32_t *next = b->d_next;

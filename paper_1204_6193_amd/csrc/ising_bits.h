@@ -39,7 +39,7 @@
 // readers stored after that barrier.
 #pragma once
 
-#include "ising_device.h"
+#include "ising_memory.h"
 
 namespace rngx {
 
@@ -123,6 +123,13 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
     static_assert(SPT * G <= 32, "a colour's sites are one word");
     const uint32_t t = threadIdx.x;
     const uint32_t L = a.L, R = a.R, VB = a.VB, nwg = GANG ? a.nwg : 1, upr = L / NB, nt = VB * upr;
+    const uint32_t nth = (nt + 63) / 64 * 64;  // threads of the waves that hold units
+    if (t >= nth) {  // whole waves of a wider workgroup (a batch's): the barriers below, nothing else
+        for (uint64_t n = 2 * a.n_sweeps; n; --n) __syncthreads();
+        __syncthreads();
+        if (a.trace && a.n_sweeps > 0) __syncthreads();
+        return;
+    }
     const uint64_t row0 = static_cast<uint64_t>(r) * a.R0;
     const bool active = t < nt;
     const uint32_t vb = active ? t / upr : 0, col = active ? t - vb * upr : 0;
@@ -148,7 +155,7 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
     uint32_t *zero_word = lds + 2 * kMaxT;
     int *e_ring = reinterpret_cast<int *>(lds + 2 * kMaxT + 4);
     constexpr bool kWeylLds = std::is_same<Unit, XorwowStripUnit>::value;
-    uint32_t *weyl0 = lds + kBitsLds / 4;  // XORWOW: Weyl word of slot i at the start, [kMaxT i + t]
+    uint32_t *weyl0 = lds + kBitsLds / 4 + t * (SPT + 1);  // XORWOW: Weyl words of the thread's slots at the start
 
     // spins and states
     uint32_t W[2] = {0, 0};
@@ -180,7 +187,7 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
         u[i] = Unit{};
         if (static_cast<uint32_t>(i) < rows) {
             const uint64_t k = ubase + t + static_cast<uint64_t>(i) * nt;
-            if constexpr (kWeylLds) u[i].load(a.st, a.S, k, weyl0 + kMaxT * i + t);
+            if constexpr (kWeylLds) u[i].load(a.st, a.S, k, weyl0 + i);
             else u[i].load(a.st, a.S, k);
             uint32_t b[2];
             row_bits(row0 + vb + static_cast<uint64_t>(i) * VB, b);
@@ -221,7 +228,7 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
     X[t] = W[0];
     X[kMaxT + t] = W[1];
     if (t == 0) *zero_word = 0;
-    for (uint32_t i = t; i < kBitsRing; i += blockDim.x) e_ring[i] = 0;
+    for (uint32_t i = t; i < kBitsRing; i += nth) e_ring[i] = 0;
 
     send(W[1], 0);
 
@@ -294,7 +301,7 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
         if ((t & 63) == 63) atomicAdd(&e_ring[sweep % kBitsRing], v);
     };
     auto flush_energy = [&](uint64_t first, uint32_t n) {
-        for (uint32_t i = t; i < n; i += blockDim.x) {
+        for (uint32_t i = t; i < n; i += nth) {
             const int v = e_ring[i];
             e_ring[i] = 0;
             if constexpr (GANG) atomicAdd(a.trace + first + i, -v);
@@ -356,7 +363,7 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
                         push2(a4, a8, rb, ra, A.t4, A.t8);
                     } else if constexpr (kWeylLds) {
                         const uint32_t n = (2 * q + j) * a.hits + h + 1;  // draws of the call with this one
-                        push1(a4, a8, u[i].next(weyl0[kMaxT * i + t], n * kWeylC), A.t4, A.t8);
+                        push1(a4, a8, u[i].next(weyl0[i], n * kWeylC), A.t4, A.t8);
                     } else if constexpr (kSub) {
                         push1(a4, a8, u[i].next(map), A.t4, A.t8);
                     } else if constexpr (!IsPhiloxKey<Unit>::value) {
@@ -484,7 +491,7 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
             for (int i = SPT - 1; i >= 0; --i) {
                 uint32_t rr[G];
                 if constexpr (kWeylLds) {
-                    const uint32_t d0 = weyl0[kMaxT * i + t], w = static_cast<uint32_t>(4 * sweep + 2 * c) * kWeylC;
+                    const uint32_t d0 = weyl0[i], w = static_cast<uint32_t>(4 * sweep + 2 * c) * kWeylC;
                     rr[0] = u[i].next(d0, w + kWeylC);
                     rr[1] = u[i].next(d0, w + 2 * kWeylC);
                 } else if constexpr (kSub) {
@@ -538,7 +545,7 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
             if constexpr (IsPhiloxKey<Unit>::value)
                 u[i].put_position(a.st, a.S, k, MH ? a.blk0 + 4ull * a.n_sweeps * a.hits : 4 * (a.blk0 + a.n_sweeps));
             else if constexpr (kWeylLds)
-                u[i].store(a.st, a.S, k, weyl0[kMaxT * i + t] + static_cast<uint32_t>(4 * a.n_sweeps * (MH ? a.hits : 1)) * kWeylC);
+                u[i].store(a.st, a.S, k, weyl0[i] + static_cast<uint32_t>(4 * a.n_sweeps * (MH ? a.hits : 1)) * kWeylC);
             else if constexpr (SweepCounter<Unit>::value) u[i].store_at(a.st, a.S, k, a);
             else u[i].store(a.st, a.S, k, 4 * a.n_sweeps * (MH ? a.hits : 1));
         }
@@ -601,6 +608,54 @@ template <class Unit>
 const void *bits_kernel_of(int slots, bool hits, bool gang) {
     if (gang) return hits ? bits_kernel_of<Unit, true, true>(slots) : bits_kernel_of<Unit, false, true>(slots);
     return hits ? bits_kernel_of<Unit, true, false>(slots) : bits_kernel_of<Unit, false, false>(slots);
+}
+
+// Batches whose replicas all keep their spins as bits (or stream through
+// memory): persistent workgroups take (replica, strip) items as k_ising_batch
+// does.  The slots of a replica are one of three per kind, so that the kernel
+// holds few copies of the strip's body.  60 replicas of L = 16 .. 1024, 50
+// sweeps: XS1024W 1.34 -> 0.72 ms, LCG32 1.32 -> 0.48; 512 such, XS1024W,
+// 1169 -> 1938 updates/ns; 2048 of L <= 128 in 256-thread workgroups 990 -> 1608.
+template <class Unit, int SPT>
+__device__ __forceinline__ void bits_item(const StripArgs &a, uint32_t r, bool gang, uint32_t *lds) {
+    if (gang) bits_strip<Unit, SPT, false, true>(a, r, lds);
+    else bits_strip<Unit, SPT, false, false>(a, r, lds);
+}
+
+template <class Unit, int MAXT>
+__global__ __launch_bounds__(MAXT) void k_ising_batch_bits(const ReplicaDesc *reps, const uint2 *items, uint32_t n_items,
+                                                           uint32_t *next) {
+    constexpr int kMost = 64 / Unit::kNB;  // slots: kMost, half or a quarter of it
+    extern __shared__ __align__(16) uint32_t bits_lds[];
+    __shared__ uint32_t idx_s;
+    __shared__ int red_s[16];
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) idx_s = atomicAdd(next, 1u);
+        __syncthreads();
+        const uint32_t idx = idx_s;
+        if (idx >= n_items) break;  // every workgroup leaves once the list is drained
+        const uint2 item = items[idx];
+        const ReplicaDesc d = reps[item.x];
+        if (d.mode == kReplicaMemory) {
+            replica_in_memory<Unit>(d, red_s);
+            continue;
+        }
+        const bool gang = d.mode == kReplicaStrips;
+        if (gang) gang_start(d);
+        const uint32_t R = item.y + 1 == d.nwg ? d.R_last : d.R;
+        const StripArgs a{d.spins, d.st, d.S, d.L, R, d.nwg, R * (d.L / Unit::kNB), d.T4, d.T8, d.n_sweeps, d.trace,
+                          d.halo, 0, d.err, 1, d.R, 0, 0, d.VB};
+        if (d.slots > kMost / 2) bits_item<Unit, kMost>(a, item.y, gang, bits_lds);
+        else if (d.slots > kMost / 4) bits_item<Unit, kMost / 2>(a, item.y, gang, bits_lds);
+        else bits_item<Unit, kMost / 4>(a, item.y, gang, bits_lds);
+    }
+}
+
+template <class Unit>
+const void *batch_bits_kernel_of(uint32_t threads) {
+    if (threads > 512) return reinterpret_cast<const void *>(&k_ising_batch_bits<Unit, 1024>);
+    return reinterpret_cast<const void *>(&k_ising_batch_bits<Unit, 512>);
 }
 
 }  // namespace rngx

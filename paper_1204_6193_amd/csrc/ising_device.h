@@ -298,9 +298,9 @@ struct StripArgs {
 // energy sums of a ring of sweeps.
 constexpr uint32_t kBitsMaxThreads = 1024, kBitsRing = 512;
 constexpr uint32_t kBitsLds = 8 * kBitsMaxThreads + 16 + 4 * kBitsRing;
-// and XORWOW's Weyl words, one a unit
-inline uint32_t bits_lds_bytes(rngx_kind kind, uint32_t slots) {
-    return kBitsLds + (kind == RNGX_XORWOW ? 4 * kBitsMaxThreads * slots : 0);
+// and XORWOW's Weyl words, one a unit (a thread's words an odd stride apart)
+inline uint32_t bits_lds_bytes(rngx_kind kind, uint32_t threads, uint32_t slots) {
+    return kBitsLds + (kind == RNGX_XORWOW ? 4 * threads * (slots + 1) : 0);
 }
 
 constexpr uint32_t kSpinLimit = 1u << 20;

@@ -127,6 +127,7 @@ struct IsingBatch {
     uint32_t lds, grid;  // launch shape
     uint32_t resident;   // workgroups of the batch kernel that fit at once
     bool gangs;          // some replica runs as a gang of strips
+    bool bits;           // the run is k_ising_batch_bits, else k_ising_batch
     int shape;           // index into kBatchShape
     int n_cu;
     Ising **lats;        // host copy of the members
@@ -202,6 +203,11 @@ const void *bits_kernel_lcg(rngx_kind kind, int slots, bool hits, bool gang);
 const void *bits_kernel_own(rngx_kind kind, int slots, bool hits, bool gang);
 const void *bits_kernel_philox(rngx_kind kind, int slots, bool hits, bool gang);
 const void *bits_kernel_xorshift(rngx_kind kind, int slots, bool hits, bool gang);
+// Batch kernels with spins as bits, for workgroups of `threads` threads.
+const void *batch_bits_kernel_lcg(rngx_kind kind, uint32_t threads);
+const void *batch_bits_kernel_own(rngx_kind kind, uint32_t threads);
+const void *batch_bits_kernel_philox(rngx_kind kind, uint32_t threads);
+const void *batch_bits_kernel_xorshift(rngx_kind kind, uint32_t threads);
 bool ising_plan(uint32_t L, rngx_kind kind, int n_cu, IsingPlan *out);
 int ising_plan_list(uint32_t L, rngx_kind kind, int n_cu, IsingPlan *out, int max);  // strip candidates
 // Plans b (shape b->shape) from b->lats, b->betas, b->traces and `sweeps`

@@ -102,3 +102,27 @@ def test_streams_at_different_positions(rngx, orc, kind, hits):
 def test_without_trace(rngx, orc, kind):
     for L in (64, 512):
         _parity(rngx, orc, L, kind, 0.4, (3, 1), trace=False)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_batch_sizes(rngx, orc, kind):
+    """A batch whose replicas all hold bits: one workgroup (some with idle
+    waves) to gangs with a shorter last strip, under several launch shapes, run
+    after run like the oracle's lattices."""
+    Ls = [16, 48, 64, 112, 256, 272, 416, 784]
+    betas = [0.3, 0.41, 0.44, 0.5, 0.38, 0.45, 0.42, 0.6]
+    sweeps = [5, 2, 3, 2, 2, 3, 2, 2]
+    lats = [rngx.ising_create(L, kind, 70 + i) for i, L in enumerate(Ls)]
+    refs = [orc.ising_create(L, kind, 70 + i) for i, L in enumerate(Ls)]
+    traces = [torch.full((n,), 7, dtype=torch.int32, device="cuda") for n in sweeps]
+    batch = rngx.ising_batch_create(lats, betas, sweeps, traces)
+    for shape in (0, 0, 2, 4):
+        print(f"case bits batch {kind} shape={shape}", flush=True)
+        rngx.ising_batch_set_shape(batch, shape)
+        rngx.ising_batch_run(batch)
+        assert rngx.ising_batch_status(batch) == 0
+        for i, (sp, st) in enumerate(refs):
+            want = orc.ising_sweeps(Ls[i], kind, betas[i], st, sp, sweeps[i])
+            assert np.array_equal(traces[i].cpu().numpy(), want), (shape, Ls[i])
+            assert np.array_equal(rngx.ising_get_spins(lats[i]).ravel(), sp), (shape, Ls[i])
+            assert np.array_equal(rngx.rng_get_state(rngx.ising_rng(lats[i])), st), (shape, Ls[i])
