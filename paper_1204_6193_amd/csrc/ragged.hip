@@ -541,31 +541,124 @@ unsigned blocks_for(uint64_t threads) { return static_cast<unsigned>((threads + 
 
 // ---------------------------------------------------------------- one stream
 // The next N outputs of ONE stream (small kinds: contiguous; XS1024W: one
-// instance in warp order) produced by many threads: chunk j of C outputs
-// (XS1024W: C instance steps) starts from the state jumped by j*C.  The
-// state is read from st_in and the final state written to st_out, a
-// different buffer, so no chunk can read what the last one writes.
-__device__ __forceinline__ void put(void *out, uint64_t idx, uint32_t u, int f32) {
-    if (f32) static_cast<float *>(out)[idx] = static_cast<float>(u >> 8) * 0x1.0p-24f;
-    else static_cast<uint32_t *>(out)[idx] = u;
+// instance in warp order).  The state is read from st_in and the final state
+// written to st_out, a different buffer, so no part can read what the last one
+// writes.  A served request is mostly short (2^10 to 2^20 values), so its time
+// is the longest chain of dependent steps in a thread: with a chunk of 4096
+// outputs per thread 2^20 values took 200-740 us on four waves.  The work is
+// spread wider instead: one wave per 4096 outputs leapfrogging (LCGs, MWC), a
+// block per thread (Philox), and for the kinds whose jumps are matrix powers
+// runs as short as a second jump allows (XORWOW from 64 outputs, XS1024W from
+// 128 steps), longer for requests that fill the device anyway.
+__device__ __forceinline__ uint32_t as_out(uint32_t u, int f32) {
+    return f32 ? __float_as_uint(static_cast<float>(u >> 8) * 0x1.0p-24f) : u;
+}
+// Values v[0..3] at positions p .. p + 3 of N (out is 16-byte aligned, p a multiple of 4).
+__device__ __forceinline__ void put4(uint32_t *out, uint64_t p, uint64_t N, const uint32_t (&v)[4], int f32) {
+    if (p + 4 <= N) {
+        const u32x4 w = {as_out(v[0], f32), as_out(v[1], f32), as_out(v[2], f32), as_out(v[3], f32)};
+        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(out + p));
+    } else {
+        for (uint32_t j = 0; j < 4; ++j)
+            if (p + j < N) out[p + j] = as_out(v[j], f32);
+    }
 }
 
+// LCG32, LCG64 (x <- a x + c) and MWC (y <- a y mod p): wave j makes values
+// 4096 j .. 4096 j + 4095, in step k lane i those from 256 k + 4 i on; its
+// states come from the chunk's jump (t64), the lane's own (lane_maps[4 i]: the
+// (4 i + 1)-step map) and the 256-step advance (lane_maps[256]).
+constexpr uint64_t kStreamChunk = 4096;
 template <class G>
-__global__ __launch_bounds__(kBlock) void k_stream_fill_small(const uint8_t *st_in, uint8_t *st_out, uint64_t N,
-                                                               uint64_t C, const uint64_t *t64, const uint32_t *t32,
-                                                               void *out, int f32, uint32_t state_words) {
+__global__ __launch_bounds__(kBlock) void k_stream_fill_wave(const uint8_t *st_in, uint8_t *st_out, uint64_t N,
+                                                              const uint64_t *t64, const uint64_t *lane_maps,
+                                                              uint32_t *out, int f32) {
+    constexpr bool kMwc = std::is_same<G, Mwc>::value, kL64 = std::is_same<G, Lcg64>::value;
+    using T = std::conditional_t<std::is_same<G, Lcg32>::value, uint32_t, uint64_t>;
+    const uint64_t j = (static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
+    const uint32_t lane = threadIdx.x & 63;
+    if (j * kStreamChunk >= N) return;  // whole waves
+    const T x0 = *reinterpret_cast<const T *>(st_in);
+    T x;
+    if constexpr (kMwc) {
+        x = mwc_mulmod(mwc_mulmod(x0, t64[j]), lane_maps[4 * lane]);
+    } else {
+        const T xc = static_cast<T>(t64[2 * j]) * x0 + static_cast<T>(t64[2 * j + 1]);
+        x = static_cast<T>(lane_maps[8 * lane]) * xc + static_cast<T>(lane_maps[8 * lane + 1]);
+    }
+    const T a1 = static_cast<T>(lane_maps[0]), c1 = static_cast<T>(lane_maps[1]);
+    const uint64_t am = lane_maps[kMwc ? kAffSpan : 2 * kAffSpan], cm = kMwc ? 0 : lane_maps[2 * kAffSpan + 1];
+    auto step = [&](T y) {
+        if constexpr (kMwc) return kMwcA * static_cast<uint32_t>(y) + (y >> 32);
+        else return static_cast<T>(a1 * y + c1);
+    };
+    const uint64_t end = min(N, (j + 1) * kStreamChunk);
+    for (uint64_t p = j * kStreamChunk + 4 * lane; p < end; p += kAffSpan) {
+        T y = x;
+        uint32_t v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = kL64 ? static_cast<uint32_t>(static_cast<uint64_t>(y) >> 32) : static_cast<uint32_t>(y);
+            if (p + i == N - 1) *reinterpret_cast<T *>(st_out) = y;  // the stream's last value
+            y = step(y);
+        }
+        put4(out, p, N, v, f32);
+        if constexpr (kMwc) x = mwc_mulmod(x, am);
+        else x = static_cast<T>(am) * x + static_cast<T>(cm);
+    }
+}
+
+// Philox: thread t makes values 4 t .. 4 t + 3, one block, or parts of two
+// when the stream does not stand at a block's first word.
+template <int ROUNDS>
+__global__ __launch_bounds__(kBlock) void k_stream_fill_philox(const uint8_t *st_in, uint8_t *st_out, uint64_t N,
+                                                                uint32_t *out, int f32) {
+    const uint64_t t = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const uint32_t *key = reinterpret_cast<const uint32_t *>(st_in);
+    const uint32_t k0 = key[0], k1 = key[1];
+    const uint64_t pos = *reinterpret_cast<const uint64_t *>(st_in + 8);
+    if (t == 0) {
+        reinterpret_cast<uint32_t *>(st_out)[0] = k0;
+        reinterpret_cast<uint32_t *>(st_out)[1] = k1;
+        *reinterpret_cast<uint64_t *>(st_out + 8) = pos + N;
+    }
+    if (4 * t >= N) return;
+    const uint64_t blk = (pos >> 2) + t;
+    const uint32_t d = static_cast<uint32_t>(pos) & 3;
+    uint32_t v[4];
+    philox_block<ROUNDS>(k0, k1, blk, v[0], v[1], v[2], v[3]);
+    if (d) {
+        uint32_t n[4];
+        philox_block<ROUNDS>(k0, k1, blk + 1, n[0], n[1], n[2], n[3]);
+        uint32_t w[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) w[i] = d + i < 4 ? pick4(v, d + i) : pick4(n, d + i - 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = w[i];
+    }
+    put4(out, 4 * t, N, v, f32);
+}
+
+// XORWOW: thread r makes the run of F outputs from r F on (F a multiple of
+// 64 that divides 4096), jumped by x^(4096 j) (t32) and x^(64 i) (fine).
+__global__ __launch_bounds__(kBlock) void k_stream_fill_xorwow(const uint8_t *st_in, uint8_t *st_out, uint64_t N,
+                                                                uint32_t F, const uint32_t *t32, const uint32_t *fine,
+                                                                uint32_t *out, int f32) {
     __shared__ uint32_t tile[kBlock / 64][64][kSeg + 1];
-    const uint64_t j = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    const uint64_t nch = (N + C - 1) / C;
+    const uint64_t r = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const uint64_t runs = (N + F - 1) / F;
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6, half = lane >> 5, col = lane & 31;
-    const bool mine = j < nch;
-    G g;
+    const bool mine = r < runs;
+    Xorwow g;
     uint32_t len = 0;
     if (mine) {
+        const uint64_t j = r * F / kStreamChunk, i = (r * F % kStreamChunk) / 64;
         g.load(st_in, 1, 0);
-        jump(g, t64, t32, j, C);
-        len = static_cast<uint32_t>(min(C, N - j * C));
+        jump(g, t32, j, kStreamChunk);
+        jump(g, fine, i, 64);
+        len = static_cast<uint32_t>(min(static_cast<uint64_t>(F), N - r * F));
     }
+    const uint64_t wave_first = r - lane;
     uint32_t rounds = (len + kSeg - 1) / kSeg;
     for (int off = 32; off > 0; off >>= 1) rounds = max(rounds, static_cast<uint32_t>(__shfl_xor(static_cast<int>(rounds), off)));
     for (uint32_t rd = 0; rd < rounds; ++rd) {
@@ -573,48 +666,48 @@ __global__ __launch_bounds__(kBlock) void k_stream_fill_small(const uint8_t *st_
         const uint32_t cnt = len > base ? min(static_cast<uint32_t>(kSeg), len - base) : 0;
         for (uint32_t k = 0; k < cnt; ++k) tile[w][lane][k] = g.next();
         __builtin_amdgcn_wave_barrier();
-        for (uint32_t q = 0; q < 64; q += 2) {
-            const uint32_t src = q + half;
-            const uint32_t len_q = static_cast<uint32_t>(__shfl(static_cast<int>(len), src));
-            const uint64_t j_q = static_cast<uint64_t>(__shfl(static_cast<long long>(j), src));
-            const uint32_t cnt_q = len_q > base ? min(static_cast<uint32_t>(kSeg), len_q - base) : 0;
-            if (col < cnt_q) put(out, j_q * C + base + col, tile[w][src][col], f32);
+#pragma unroll 4
+        for (uint32_t q = 0; q < 64; q += 2) {  // two lanes' segments per store
+            const uint64_t at = (wave_first + q + half) * F + base + col;
+            if (at < N) out[at] = as_out(tile[w][q + half][col], f32);
         }
         __builtin_amdgcn_wave_barrier();
     }
-    if (mine && j == nch - 1) {
-        // the whole one-stream image first: a generator's store writes only
-        // what it changes (Philox: the position, not the key)
-        for (uint32_t i = 0; i < state_words; ++i)
-            reinterpret_cast<uint32_t *>(st_out)[i] = reinterpret_cast<const uint32_t *>(st_in)[i];
-        g.store(st_out, 1, 0);
-    }
+    if (mine && r == runs - 1) g.store(st_out, 1, 0);
 }
 
 // XS1024W instance (state: 32 words, step counter, Weyl seed): one 16-lane
-// DPP row per chunk of C steps.
+// DPP row per run of F steps (a multiple of 128 that divides 4096), jumped by
+// x^(4096 j) (t32) and x^(128 i) (fine).
 __global__ __launch_bounds__(kBlock) void k_stream_fill_xs(const uint8_t *st_in, uint8_t *st_out, uint64_t N,
-                                                            uint64_t C, const uint32_t *t32, void *out, int f32) {
+                                                            uint32_t F, const uint32_t *t32, const uint32_t *fine,
+                                                            uint32_t *out, int f32) {
     const uint64_t t = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    const uint64_t j = t >> 4, lane = t & 15;
-    const uint64_t total_steps = (N + 31) / 32, nch = (total_steps + C - 1) / C;
-    if (j >= nch) return;  // whole rows
+    const uint64_t r = t >> 4, lane = t & 15;
+    const uint64_t total_steps = (N + 31) / 32, runs = (total_steps + F - 1) / F;
+    if (r >= runs) return;  // whole rows
     const uint2 w = reinterpret_cast<const uint2 *>(st_in)[lane];
     uint32_t a = w.x, b = w.y;
+    const uint64_t first = r * F, j = first / kStreamChunk, i = (first % kStreamChunk) / 128;
     if (j) xs1024_apply_poly(t32 + 32 * j, a, b);
+    if (i) xs1024_apply_poly(fine + 32 * i, a, b);
     const uint64_t n0 = *reinterpret_cast<const uint64_t *>(st_in + 128);
     const uint32_t y0 = *reinterpret_cast<const uint32_t *>(st_in + 136);
-    uint32_t y = y0 + static_cast<uint32_t>(n0 + j * C) * kWeylC;
-    const uint64_t steps = min(C, total_steps - j * C);
+    uint32_t y = y0 + static_cast<uint32_t>(n0 + first) * kWeylC;
+    const uint64_t steps = min(static_cast<uint64_t>(F), total_steps - first);
     for (uint64_t k = 0; k < steps; ++k) {
         xs1024_step(a, b);
         y += kWeylC;
         const uint32_t m = weyl_mix(y);
-        const uint64_t v = 32 * (j * C + k) + 2 * lane;
-        if (v < N) put(out, v, a + m, f32);
-        if (v + 1 < N) put(out, v + 1, b + m, f32);
+        const uint64_t v = 32 * (first + k) + 2 * lane;
+        const uint32_t u0 = as_out(a + m, f32), u1 = as_out(b + m, f32);
+        if (v + 1 < N) {
+            __builtin_nontemporal_store(u0 | static_cast<uint64_t>(u1) << 32, reinterpret_cast<uint64_t *>(out + v));
+        } else if (v < N) {
+            out[v] = u0;
+        }
     }
-    if (j == nch - 1) {
+    if (r == runs - 1) {
         reinterpret_cast<uint2 *>(st_out)[lane] = make_uint2(a, b);
         if (lane == 0) {
             *reinterpret_cast<uint64_t *>(st_out + 128) = n0 + total_steps;
@@ -623,29 +716,60 @@ __global__ __launch_bounds__(kBlock) void k_stream_fill_xs(const uint8_t *st_in,
     }
 }
 
+// The shortest run (a power of two times `least`, at most 4096) that makes no
+// more than `most` runs of `total`: a run pays for its jumps (XORWOW 320 steps,
+// XS1024W 2048), so more of them than the device runs at once cost more than
+// their shorter chains save.
+uint32_t run_length(uint64_t total, uint32_t least, uint64_t most) {
+    uint32_t F = least;
+    while (F < kStreamChunk && (total + F - 1) / F > most) F *= 2;
+    return F;
+}
+
 }  // namespace
 
-uint64_t stream_fill_chunk(rngx_kind) { return 4096; }
+uint64_t stream_fill_chunk(rngx_kind) { return kStreamChunk; }
+
+void stream_fill_fine(rngx_kind kind, std::vector<uint64_t> *u64s, std::vector<uint32_t> *u32s) {
+    u64s->clear();
+    u32s->clear();
+    switch (kind) {
+    case RNGX_LCG32:
+    case RNGX_LCG64:
+    case RNGX_MWC: {
+        Gen g{};
+        g.kind = kind;
+        ragged_lane_maps(&g, u64s);
+        break;
+    }
+    case RNGX_XORWOW: jump_table(kind, 64, kStreamChunk / 64, u64s, u32s); break;
+    case RNGX_XS1024W: jump_table(kind, 128, kStreamChunk / 128, u64s, u32s); break;
+    default: break;  // Philox: counters
+    }
+}
 
 hipError_t launch_stream_fill(rngx_kind kind, const uint8_t *st_in, uint8_t *st_out, uint64_t N, int f32,
-                              const uint64_t *t64, const uint32_t *t32, void *out, hipStream_t st) {
+                              const StreamTables &tb, void *out_, hipStream_t st) {
     if (N == 0) return hipSuccess;
-    const uint64_t C = stream_fill_chunk(kind);
-    if (kind == RNGX_XS1024W) {
-        const uint64_t nch = ((N + 31) / 32 + C - 1) / C;
-        hipLaunchKernelGGL(k_stream_fill_xs, dim3(blocks_for(16 * nch)), dim3(kBlock), 0, st, st_in, st_out, N, C, t32,
-                           out, f32);
-        return hipGetLastError();
-    }
-    const unsigned blocks = blocks_for((N + C - 1) / C);
-    const uint32_t w = static_cast<uint32_t>(state_bytes(kind, 1) / 4);
+    uint32_t *out = static_cast<uint32_t *>(out_);
+    const dim3 block(kBlock), waves(blocks_for(64 * ((N + kStreamChunk - 1) / kStreamChunk))), quads(blocks_for((N + 3) / 4));
     switch (kind) {
-    case RNGX_LCG32: hipLaunchKernelGGL(k_stream_fill_small<Lcg32>, dim3(blocks), dim3(kBlock), 0, st, st_in, st_out, N, C, t64, t32, out, f32, w); break;
-    case RNGX_LCG64: hipLaunchKernelGGL(k_stream_fill_small<Lcg64>, dim3(blocks), dim3(kBlock), 0, st, st_in, st_out, N, C, t64, t32, out, f32, w); break;
-    case RNGX_MWC: hipLaunchKernelGGL(k_stream_fill_small<Mwc>, dim3(blocks), dim3(kBlock), 0, st, st_in, st_out, N, C, t64, t32, out, f32, w); break;
-    case RNGX_XORWOW: hipLaunchKernelGGL(k_stream_fill_small<Xorwow>, dim3(blocks), dim3(kBlock), 0, st, st_in, st_out, N, C, t64, t32, out, f32, w); break;
-    case RNGX_PHILOX4X32_10: hipLaunchKernelGGL(k_stream_fill_small<Philox>, dim3(blocks), dim3(kBlock), 0, st, st_in, st_out, N, C, t64, t32, out, f32, w); break;
-    case RNGX_PHILOX4X32_7: hipLaunchKernelGGL(k_stream_fill_small<Philox7>, dim3(blocks), dim3(kBlock), 0, st, st_in, st_out, N, C, t64, t32, out, f32, w); break;
+    case RNGX_LCG32: hipLaunchKernelGGL(k_stream_fill_wave<Lcg32>, waves, block, 0, st, st_in, st_out, N, tb.t64, tb.lane, out, f32); break;
+    case RNGX_LCG64: hipLaunchKernelGGL(k_stream_fill_wave<Lcg64>, waves, block, 0, st, st_in, st_out, N, tb.t64, tb.lane, out, f32); break;
+    case RNGX_MWC: hipLaunchKernelGGL(k_stream_fill_wave<Mwc>, waves, block, 0, st, st_in, st_out, N, tb.t64, tb.lane, out, f32); break;
+    case RNGX_PHILOX4X32_10: hipLaunchKernelGGL(k_stream_fill_philox<10>, quads, block, 0, st, st_in, st_out, N, out, f32); break;
+    case RNGX_PHILOX4X32_7: hipLaunchKernelGGL(k_stream_fill_philox<7>, quads, block, 0, st, st_in, st_out, N, out, f32); break;
+    case RNGX_XORWOW: {
+        const uint32_t F = run_length(N, 64, 65536);
+        hipLaunchKernelGGL(k_stream_fill_xorwow, dim3(blocks_for((N + F - 1) / F)), block, 0, st, st_in, st_out, N, F, tb.t32, tb.fine, out, f32);
+        break;
+    }
+    case RNGX_XS1024W: {
+        const uint64_t steps = (N + 31) / 32;
+        const uint32_t F = run_length(steps, 128, 2048);
+        hipLaunchKernelGGL(k_stream_fill_xs, dim3(blocks_for(16 * ((steps + F - 1) / F))), block, 0, st, st_in, st_out, N, F, tb.t32, tb.fine, out, f32);
+        break;
+    }
     default: break;
     }
     return hipGetLastError();

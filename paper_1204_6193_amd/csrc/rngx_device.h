@@ -391,30 +391,13 @@ __device__ __forceinline__ void xorwow_apply_poly(const uint32_t *c, uint32_t (&
     for (int q = 0; q < 5; ++q) s[q] = acc[q];
 }
 
-// Jumps by j*C outputs with tables made by jump_table(kind, C, ...):
-// t64 = affine pairs (LCG) or a^(jC) mod p (MWC), t32 = x^(jC) mod P
-// polynomials (XORWOW).  Philox needs none.
-__device__ __forceinline__ uint64_t mwc_mulmod(uint64_t y, uint64_t A);
-__device__ __forceinline__ void jump(Lcg32 &g, const uint64_t *t64, const uint32_t *, uint64_t j, uint64_t) {
-    g.x = static_cast<uint32_t>(t64[2 * j]) * g.x + static_cast<uint32_t>(t64[2 * j + 1]);
-}
-__device__ __forceinline__ void jump(Lcg64 &g, const uint64_t *t64, const uint32_t *, uint64_t j, uint64_t) {
-    g.x = t64[2 * j] * g.x + t64[2 * j + 1];
-}
-__device__ __forceinline__ void jump(Mwc &g, const uint64_t *t64, const uint32_t *, uint64_t j, uint64_t) {
-    g.y = mwc_mulmod(g.y, t64[j]);
-}
-__device__ __forceinline__ void jump(Xorwow &g, const uint64_t *, const uint32_t *t32, uint64_t j, uint64_t C) {
+// Jump by j*C outputs with the table x^(jC) mod P made by jump_table(XORWOW, C, ...).
+__device__ __forceinline__ void jump(Xorwow &g, const uint32_t *t32, uint64_t j, uint64_t C) {
     if (!j) return;
     uint32_t s[5] = {g.x, g.y, g.z, g.w, g.v};
     xorwow_apply_poly(t32 + 5 * j, s);
     g.x = s[0]; g.y = s[1]; g.z = s[2]; g.w = s[3]; g.v = s[4];
     g.d += static_cast<uint32_t>(j * C) * kWeylC;
-}
-template <int ROUNDS>
-__device__ __forceinline__ void jump(PhiloxR<ROUNDS> &g, const uint64_t *, const uint32_t *, uint64_t j, uint64_t C) {
-    g.pos += j * C;
-    if (g.pos & 3) philox_block<ROUNDS>(g.k0, g.k1, g.pos >> 2, g.b0, g.b1, g.b2, g.b3);  // resume mid-block
 }
 
 // y * A mod p for the MWC modulus p = a 2^32 - 1, using 2^64 = R (mod p)

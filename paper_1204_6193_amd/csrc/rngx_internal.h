@@ -243,9 +243,17 @@ void ragged_lane_maps(const Gen *g, std::vector<uint64_t> *lane);  // affine kin
 // plans on the host and stages the plan in the device's static scratch.
 rngx_status ragged_fill_noalloc(Gen *g, const uint64_t *offsets, uint64_t units, uint32_t *d_out, hipStream_t st);
 hipError_t launch_ragged(Ragged *r, uint32_t *d_out, hipStream_t st);
+// One stream's next N values (a served fill), `out` 16-byte aligned.  Tables
+// of a kind: jumps of stream_fill_chunk outputs (XS1024W: steps; jump_table),
+// and what stream_fill_fine makes for the places inside a chunk.
+struct StreamTables {
+    const uint64_t *t64, *lane;
+    const uint32_t *t32, *fine;
+};
 uint64_t stream_fill_chunk(rngx_kind kind);
+void stream_fill_fine(rngx_kind kind, std::vector<uint64_t> *u64s, std::vector<uint32_t> *u32s);
 hipError_t launch_stream_fill(rngx_kind kind, const uint8_t *st_in, uint8_t *st_out, uint64_t N, int f32,
-                              const uint64_t *t64, const uint32_t *t32, void *out, hipStream_t st);
+                              const StreamTables &tb, void *out, hipStream_t st);
 uint64_t ising_partials(uint32_t L);
 
 

@@ -129,8 +129,8 @@ struct Server {
     std::vector<std::shared_ptr<ServerRequest>> launching;  // admitted, being launched (lock released)
     std::unordered_map<uint64_t, std::shared_ptr<ServerRequest>> all;
     std::map<std::pair<uint32_t, int>, ClientGen *> gens;
-    const uint64_t *t64[8] = {};  // per-kind jump tables for chunks of stream_fill_chunk(kind)
-    const uint32_t *t32[8] = {};
+    StreamTables tables[8] = {};  // per kind; the jump tables in the pool, the fine ones in d_fine
+    void *d_fine[8] = {};
     std::unordered_map<uint32_t, uint64_t> ising_count;
     std::deque<uint64_t> completed;  // finished tickets not yet returned by wait_any
     uint64_t next_ticket = 1;
@@ -197,8 +197,8 @@ bool launch_request(Server *s, ServerRequest &r, ClientGen *c) {
     if (r.type == 0) {
         if (!c) return false;
         r.n_values = r.count;
-        if (launch_stream_fill(r.kind, c->buf[c->cur], c->buf[c->cur ^ 1], r.count, r.f32, s->t64[r.kind],
-                               s->t32[r.kind], base, st) != hipSuccess)
+        if (launch_stream_fill(r.kind, c->buf[c->cur], c->buf[c->cur ^ 1], r.count, r.f32, s->tables[r.kind],
+                               base, st) != hipSuccess)
             return false;
         c->cur ^= 1;  // requests of one client and kind are launched in order on one stream
     } else {
@@ -306,6 +306,13 @@ void worker_loop(Server *s) {
 
 }  // namespace
 
+static void free_fine(Server *s) {
+    for (void *&p : s->d_fine) {
+        (void)hipFree(p);
+        p = nullptr;
+    }
+}
+
 rngx_status server_create(const rngx_server_config *cfg, Server **out) {
     Server *s = new Server{};
     s->cfg = *cfg;
@@ -334,18 +341,33 @@ rngx_status server_create(const rngx_server_config *cfg, Server **out) {
                                                                        : static_cast<const void *>(t32.data()),
                                                bytes, hipMemcpyHostToDevice) != hipSuccess) {
                 (void)hipGetLastError();
+                free_fine(s);
                 delete s;
                 return fail(RNGX_E_NOMEM, "memory budget too small for the jump tables");
             }
-            if (w == 0) s->t64[k] = reinterpret_cast<const uint64_t *>(s->pool.ptr(off));
-            else s->t32[k] = reinterpret_cast<const uint32_t *>(s->pool.ptr(off));
+            if (w == 0) s->tables[k].t64 = reinterpret_cast<const uint64_t *>(s->pool.ptr(off));
+            else s->tables[k].t32 = reinterpret_cast<const uint32_t *>(s->pool.ptr(off));
         }
+        stream_fill_fine(kind, &t64, &t32);
+        const uint64_t bytes = 8 * t64.size() + 4 * t32.size();  // one of the two
+        if (!bytes) continue;
+        if (hipMalloc(&s->d_fine[k], bytes) != hipSuccess ||
+            hipMemcpy(s->d_fine[k], t64.empty() ? static_cast<const void *>(t32.data()) : static_cast<const void *>(t64.data()),
+                      bytes, hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipGetLastError();
+            free_fine(s);
+            delete s;
+            return fail(RNGX_E_NOMEM, "device memory for the jump tables");
+        }
+        s->tables[k].lane = static_cast<const uint64_t *>(s->d_fine[k]);
+        s->tables[k].fine = static_cast<const uint32_t *>(s->d_fine[k]);
     }
     for (uint32_t i = 0; i < cfg->slots; ++i) {
         hipStream_t st;
         if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) {
             (void)hipGetLastError();
             for (auto x : s->streams) (void)hipStreamDestroy(x);
+            free_fine(s);
             delete s;
             return fail(RNGX_E_HIP, "stream creation failed");
         }
@@ -529,6 +551,7 @@ void server_destroy(Server *s) {
     for (auto e : s->spare_events) (void)hipEventDestroy(e);
     for (auto &kv : s->all)
         if (kv.second->ev) (void)hipEventDestroy(kv.second->ev);
+    free_fine(s);
     delete s;
 }
 

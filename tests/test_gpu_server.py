@@ -253,3 +253,25 @@ def test_server_small_requests_pass_a_blocked_one(rngx, orc):
     srv.release(big)
     srv.release(same)
     srv.destroy()
+
+
+@pytest.mark.parametrize("kind", ["lcg32", "lcg64", "mwc", "xorwow", "philox4x32_10", "philox4x32_7", "xs1024w"])
+def test_server_fill_lengths(rngx, orc, kind):
+    """Lengths around every unit a served fill is cut into (a lane's four
+    values, a 256-value store, 64-output and 128-step runs, a 4096-output
+    chunk, longer runs for a long request), one after another on one stream."""
+    u = _unit(kind)
+    srv = rngx.Server(slots=2, max_inflight=4, memory_budget=128 << 20, seed=SEED)
+    st = orc.seed(kind, u, orc.splitmix(SEED, 16 * 2 + rngx.KINDS[kind]))
+    lengths = [1, 3, 4, 5, 63, 64, 65, 255, 257, 2048, 4095, 4096, 4097, 8192 + 62, 100_003, 131_072, 131_073, 5_000_001]
+    for i, n in enumerate(lengths):
+        print(f"case served fill {kind} n={n}", flush=True)
+        host, _ = _result_bytes(rngx, srv, srv.submit_fill(2, kind, n, i % 2 == 1), 4 * n)
+        want = orc.generate(kind, u, st, -(-n // u)).reshape(-1)[:n]
+        if i % 2:
+            want = (want >> 8).astype(np.float32) * np.float32(2.0 ** -24)
+            assert np.array_equal(host.view(np.float32), want), (kind, n)
+        else:
+            assert np.array_equal(host.view(np.uint32), want), (kind, n)
+    assert np.array_equal(srv.get_client_state(2, kind), st), kind
+    srv.destroy()
