@@ -12,6 +12,7 @@
 //   of the paper's product with a stored 1024 x 1024 bit matrix.  The Weyl
 //   parts advance in closed form (d += n c; the XS1024W step counter += n).
 // Philox: the position advances by n.
+#include <array>
 #include <mutex>
 #include <vector>
 
@@ -173,6 +174,95 @@ const Poly &xorwow_minpoly() {
     return P;
 }
 
+// Arithmetic modulo the 1024-bit P.  A jump's polynomial is host work before
+// its kernel can start, and bit-serial squaring and reduction of x^n took
+// 500 us of a 600 us jump.  Products go a nibble of one factor at a time,
+// reductions a nibble of the high half (table of nibble x^(1024 + 4 k) mod P),
+// and x^n is a product of at most 16 powers from a table of x^(d 16^k): about
+// 40 us.  The tables (512 KB and 32 KB) are made once per process.
+struct Xs1024Field {
+    static constexpr int W = 16;  // words
+    using Elem = std::array<uint64_t, W>;
+    std::vector<Elem> red;  // [16 k + nibble]
+    std::vector<Elem> pow;  // [16 k + d]: x^(d 16^k) mod P
+
+    Xs1024Field() {
+        Elem low{};  // x^1024 mod P
+        for (int w = 0; w < W; ++w) low[w] = xs1024_minpoly()[w];
+        red.resize(256 * 16);
+        Elem x = low;
+        for (int k = 0; k < 256; ++k) {
+            for (int bit = 0; bit < 4; ++bit) {
+                for (int d = 1 << bit; d < 2 << bit; ++d)
+                    for (int w = 0; w < W; ++w) red[16 * k + d][w] = red[16 * k + d - (1 << bit)][w] ^ x[w];
+                const bool top = x[W - 1] >> 63;
+                for (int w = W - 1; w > 0; --w) x[w] = x[w] << 1 | x[w - 1] >> 63;
+                x[0] <<= 1;
+                if (top)
+                    for (int w = 0; w < W; ++w) x[w] ^= low[w];
+            }
+        }
+        pow.resize(16 * 16);
+        Elem base{};
+        base[0] = 2;  // x
+        for (int k = 0; k < 16; ++k) {
+            pow[16 * k][0] = 1;
+            for (int d = 1; d < 16; ++d) pow[16 * k + d] = d == 1 ? base : mul(pow[16 * k + d - 1], base);
+            base = mul(pow[16 * k + 15], base);
+        }
+    }
+    Elem mul(const Elem &a, const Elem &b) const {
+        uint64_t t[16][W + 1] = {};  // nibble times b
+        for (int w = 0; w < W; ++w) t[1][w] = b[w];
+        for (int d = 2; d < 16; d += 2) {
+            t[d][0] = t[d / 2][0] << 1;
+            for (int w = 1; w <= W; ++w) t[d][w] = t[d / 2][w] << 1 | t[d / 2][w - 1] >> 63;
+            for (int w = 0; w <= W; ++w) t[d + 1][w] = t[d][w] ^ t[1][w];
+        }
+        uint64_t r[2 * W + 1] = {};
+        for (int s = 60; s >= 0; s -= 4) {
+            if (s != 60) {
+                for (int w = 2 * W; w > 0; --w) r[w] = r[w] << 4 | r[w - 1] >> 60;
+                r[0] <<= 4;
+            }
+            for (int i = 0; i < W; ++i) {
+                const uint64_t *x = t[(a[i] >> s) & 15];
+                for (int w = 0; w <= W; ++w) r[i + w] ^= x[w];
+            }
+        }
+        Elem out;
+        for (int w = 0; w < W; ++w) out[w] = r[w];
+        for (int k = 0; k < 256; ++k) {
+            const Elem &x = red[16 * k + ((r[W + k / 16] >> (4 * (k % 16))) & 15)];
+            for (int w = 0; w < W; ++w) out[w] ^= x[w];
+        }
+        return out;
+    }
+    Elem x_pow(uint64_t n) const {
+        Elem r{};
+        r[0] = 1;
+        bool one = true;
+        for (int k = 0; n; ++k, n >>= 4) {
+            if (!(n & 15)) continue;
+            const Elem &p = pow[16 * k + (n & 15)];
+            r = one ? p : mul(r, p);
+            one = false;
+        }
+        return r;
+    }
+};
+const Xs1024Field &xs1024_field() {
+    static const Xs1024Field f;
+    return f;
+}
+// Coefficient i at bit i%32 of c[i/32].
+void xs1024_words(const Xs1024Field::Elem &e, uint32_t *c) {
+    for (int w = 0; w < Xs1024Field::W; ++w) {
+        c[2 * w] = static_cast<uint32_t>(e[w]);
+        c[2 * w + 1] = static_cast<uint32_t>(e[w] >> 32);
+    }
+}
+
 // ---------------------------------------------------------------- kernels
 struct JumpPoly1024 { uint32_t c[32]; };  // coefficient i at bit i%32 of c[i/32]
 struct JumpPoly160 { uint32_t c[5]; };
@@ -253,17 +343,28 @@ uint64_t host_powmod_p(uint64_t a, uint64_t n) {
 
 unsigned blocks_for(uint64_t threads) { return static_cast<unsigned>((threads + kBlock - 1) / kBlock); }
 
-template <int NBITS>
-void poly_table(const Poly &P, uint64_t step, uint64_t count, std::vector<uint32_t> *out) {
-    constexpr int NW = NBITS / 32;
-    out->assign(count * NW, 0);
+// x^(j step) mod P for j < count, packed.
+void xorwow_table(uint64_t step, uint64_t count, std::vector<uint32_t> *out) {
+    const Poly &P = xorwow_minpoly();
+    out->assign(count * 5, 0);
     const Poly xs = x_pow_mod(step, P);
     Poly cur(P.size(), 0);
     cur[0] = 1;  // x^0
     for (uint64_t j = 0; j < count; ++j) {
-        for (int i = 0; i < NBITS; ++i)
-            if (poly_bit(cur, i)) (*out)[j * NW + i / 32] |= 1u << (i % 32);
+        for (int i = 0; i < 160; ++i)
+            if (poly_bit(cur, i)) (*out)[j * 5 + i / 32] |= 1u << (i % 32);
         cur = poly_mulmod(cur, xs, P);
+    }
+}
+void xs1024_table(uint64_t step, uint64_t count, std::vector<uint32_t> *out) {
+    const Xs1024Field &F = xs1024_field();
+    out->assign(count * 32, 0);
+    const Xs1024Field::Elem xs = F.x_pow(step);
+    Xs1024Field::Elem cur{};
+    cur[0] = 1;  // x^0
+    for (uint64_t j = 0; j < count; ++j) {
+        xs1024_words(cur, out->data() + 32 * j);
+        if (j + 1 < count) cur = F.mul(cur, xs);
     }
 }
 
@@ -295,8 +396,8 @@ void jump_table(rngx_kind kind, uint64_t step, uint64_t count, std::vector<uint6
         }
         break;
     }
-    case RNGX_XORWOW: poly_table<160>(xorwow_minpoly(), step, count, u32s); break;
-    case RNGX_XS1024W: poly_table<1024>(xs1024_minpoly(), step, count, u32s); break;
+    case RNGX_XORWOW: xorwow_table(step, count, u32s); break;
+    case RNGX_XS1024W: xs1024_table(step, count, u32s); break;
     case RNGX_PHILOX4X32_7:
     case RNGX_PHILOX4X32_10:
     case RNGX_MWC_DIFF: break;  // counter; per-stream powers computed on the device
@@ -370,9 +471,8 @@ hipError_t launch_skip(Gen *g, uint64_t n, hipStream_t st) {
         break;
     }
     case RNGX_XS1024W: {
-        const Poly J = x_pow_mod(n, xs1024_minpoly());
-        JumpPoly1024 jp{};
-        for (int i = 0; i < 1024; ++i) if (poly_bit(J, i)) jp.c[i / 32] |= 1u << (i % 32);
+        JumpPoly1024 jp;
+        xs1024_words(xs1024_field().x_pow(n), jp.c);
         hipLaunchKernelGGL(k_skip_xs, dim3(blocks_for(S / 2)), dim3(kBlock), 0, st, g->d_state, S, jp, n);
         break;
     }

@@ -367,14 +367,25 @@ __device__ __forceinline__ uint32_t weyl_mix(uint32_t y) { return y ^ (y >> 16);
 
 // J(M) v for the XS1024W transition matrix M and J(x) = sum c_i x^i
 // (coefficient i at bit i%32 of c[i/32], degree < 1024), by Horner's rule:
-// 1024 generator steps.  (a, b) is the calling lane's word pair of v.
+// 1024 generator steps.  (a, b) is the calling lane's word pair of v.  A
+// chain of 17 dependent instructions a step: the coefficient word is fetched
+// one word ahead and its bit taken as a mask, so that no step waits for a load
+// or a branch (a load and a test in every step took 46 ns a step on one wave).
 __device__ __forceinline__ void xs1024_apply_poly(const uint32_t *c, uint32_t &a, uint32_t &b) {
     const uint32_t va = a, vb = b;
     a = 0;
     b = 0;
-    for (int i = 1023; i >= 0; --i) {
-        xs1024_step(a, b);
-        if ((c[i >> 5] >> (i & 31)) & 1u) { a ^= va; b ^= vb; }
+    uint32_t next = c[31];
+    for (int w = 31; w >= 0; --w) {
+        const uint32_t word = next;
+        next = c[w ? w - 1 : 0];
+#pragma unroll
+        for (int i = 31; i >= 0; --i) {
+            xs1024_step(a, b);
+            const uint32_t m = static_cast<uint32_t>(static_cast<int32_t>(word << (31 - i)) >> 31);
+            a ^= va & m;
+            b ^= vb & m;
+        }
     }
 }
 
