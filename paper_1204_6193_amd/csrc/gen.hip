@@ -97,46 +97,144 @@ __global__ __launch_bounds__(kBlock) void k_seed_xs(uint8_t *st, uint64_t S, uin
 __device__ __forceinline__ float to_unit(uint32_t u) { return static_cast<float>(u >> 8) * 0x1.0p-24f; }
 
 // Non-temporal stores: the outputs are streamed out and not read back by
-// this kernel (XS1024W u32 fill at 2^20 x 4096: 6.30 -> 6.55 TB/s).
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// this kernel (XS1024W u32 fill at 2^20 x 4096: 6.30 -> 6.55 TB/s).  Plain ones
+// (NT = false) where waves put a row's lines together and the output fits the
+// memory-side cache: LCG32 99991 x 400 43 -> 39 us on buffers taken in turn (38
+// -> 28 on one), but 300001 x 1000 (1.2 GB) 235 -> 258.
+// A row of S words starts at any word when S is not a multiple of V; global
+// stores of 2 and 4 words need no more than word alignment.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(4)));
 
-template <int MODE, int V>
-__device__ __forceinline__ void store_out(void *out, uint64_t idx, const uint32_t (&u)[V]) {
+// The first n of V words (n = V: one store).
+template <int MODE, int V, bool NT = true>
+__device__ __forceinline__ void store_out(void *out, uint64_t idx, const uint32_t (&u)[V], uint32_t n = V) {
     uint32_t w[V];
     for (int v = 0; v < V; ++v) w[v] = MODE == kOutU32 ? u[v] : __float_as_uint(to_unit(u[v]));
     uint32_t *o = static_cast<uint32_t *>(out) + idx;
-    if constexpr (V == 4) {
-        const u32x4 x = {w[0], w[1], w[2], w[3]};
-        __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(o));
-    } else if constexpr (V == 2) {
-        __builtin_nontemporal_store(w[0] | static_cast<uint64_t>(w[1]) << 32, reinterpret_cast<uint64_t *>(o));
+    if (n == V) {
+        if constexpr (V == 4) {
+            const u32x4 x = {w[0], w[1], w[2], w[3]};
+            if constexpr (NT) __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(o));
+            else *reinterpret_cast<u32x4 *>(o) = x;
+        } else if constexpr (V == 2) {
+            const u32x2 x = {w[0], w[1]};
+            __builtin_nontemporal_store(x, reinterpret_cast<u32x2 *>(o));
+        } else {
+            if constexpr (NT) __builtin_nontemporal_store(w[0], o);
+            else *o = w[0];
+        }
     } else {
-        __builtin_nontemporal_store(w[0], o);
+        for (uint32_t v = 0; v < V; ++v)
+            if (v < n) o[v] = w[v];
     }
 }
 
-// Small-state kinds: V consecutive streams per thread.
-template <class G, int MODE, int V>
-__global__ __launch_bounds__(kBlock) void k_fill_small(uint8_t *st, uint64_t S, uint64_t count, void *out) {
+// The state n outputs on, for the kinds that get there in a few dozen
+// instructions.
+template <class G> struct HasAdvance : std::false_type {};
+template <> struct HasAdvance<Lcg32> : std::true_type {};
+template <> struct HasAdvance<Lcg64> : std::true_type {};
+template <> struct HasAdvance<Lcg32Sub> : std::true_type {};
+template <> struct HasAdvance<Lcg64Sub> : std::true_type {};
+template <> struct HasAdvance<Mwc> : std::true_type {};
+template <> struct HasAdvance<MwcDiff> : std::true_type {};
+template <int ROUNDS> struct HasAdvance<PhiloxR<ROUNDS>> : std::true_type {};
+
+// The multiplier (MWC: a^n mod p) and increment of n steps, the same for all
+// streams of a fill but MWC_DIFF's and the sub-stream LCGs', which the device
+// works out.
+struct RowMap {
+    uint64_t a, c;
+};
+template <class G>
+__device__ __forceinline__ RowMap row_map(const G &g, uint64_t n) {
+    RowMap m{1, 0};
+    if constexpr (std::is_same<G, Lcg32>::value) affine_power(kLcg32A, kLcg32C, n, &m.a, &m.c);
+    else if constexpr (std::is_same<G, Lcg64>::value) affine_power(kLcg64A, kLcg64C, n, &m.a, &m.c);
+    else if constexpr (std::is_same<G, Lcg32Sub>::value || std::is_same<G, Lcg64Sub>::value) affine_power(g.A, g.C, n, &m.a, &m.c);
+    else if constexpr (std::is_same<G, Mwc>::value) {
+        uint64_t b = kMwcA;
+        for (; n; n >>= 1) {
+            if (n & 1) m.a = mwc_mulmod(m.a, b);
+            b = mwc_mulmod(b, b);
+        }
+    }
+    return m;
+}
+template <class G>
+__device__ __forceinline__ void advance(G &g, const RowMap &m, uint64_t n) {
+    if constexpr (std::is_same<G, Mwc>::value) g.y = mwc_mulmod(g.y, m.a);
+    else if constexpr (std::is_same<G, MwcDiff>::value) g.y = mwc_jump_mod(g.y, g.a, n);
+    else g.x = static_cast<decltype(g.x)>(m.a * g.x + m.c);
+}
+template <int ROUNDS>
+__device__ __forceinline__ void advance(PhiloxR<ROUNDS> &g, const RowMap &, uint64_t n) {
+    g.pos += n;
+    if (g.pos & 3) philox_block<ROUNDS>(g.k0, g.k1, g.pos >> 2, g.b0, g.b1, g.b2, g.b3);  // resume mid-block
+}
+
+// Small-state kinds: V consecutive streams per thread.  With SPLIT, row block
+// blockIdx.y of `rows` rows: its threads start from their streams' states
+// blockIdx.y * rows outputs on (a fill of few streams and many rows would
+// otherwise run a few long chains).  The row blocks of a group of streams count
+// themselves in arrived[blockIdx.x] once their states are loaded; the one that
+// comes last writes the states after the fill, and a zero for the next fill.
+template <class G, int MODE, int V, bool SPLIT, bool NT>
+__global__ __launch_bounds__(kBlock) void k_fill_small(uint8_t *st, uint64_t S, uint64_t count, void *out,
+                                                       uint64_t rows, uint32_t *arrived) {
     const uint64_t s0 = (static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * V;
-    if (s0 >= S) return;
+    if (!SPLIT && s0 >= S) return;
+    const uint32_t live = s0 < S ? static_cast<uint32_t>(min(static_cast<uint64_t>(V), S - s0)) : 0;
     G g[V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) g[v].load(st, S, s0 + v);
+    for (int v = 0; v < V; ++v) {
+        g[v] = G{};
+        if (v < live) g[v].load(st, S, s0 + v);
+    }
+    uint64_t k = 0, end = count;
+    if constexpr (SPLIT) {
+        k = blockIdx.y * rows;
+        end = min(count, k + rows);
+        __shared__ uint32_t last;
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // the loads are complete
+        __syncthreads();
+        if (threadIdx.x == 0)
+            last = __hip_atomic_fetch_add(arrived + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.y - 1;
+        __syncthreads();
+        if (last) {
+            const RowMap m = row_map(g[0], count);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                G f = g[v];
+                if (v < live) {
+                    advance(f, m, count);
+                    f.store(st, S, s0 + v);
+                }
+            }
+            if (threadIdx.x == 0) arrived[blockIdx.x] = 0;
+        }
+        if (!live) return;
+        if (k) {
+            const RowMap m = row_map(g[0], k);
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (v < live) advance(g[v], m, k);
+        }
+    }
     uint32_t acc[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) acc[v] = 0;
-    auto emit = [&](uint64_t k, const uint32_t (&u)[V]) {
+    auto emit = [&](uint64_t row, const uint32_t (&u)[V]) {
         if constexpr (MODE == kOutXor) {
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[v] ^= u[v];
         } else {
-            store_out<MODE, V>(out, k * S + s0, u);
+            store_out<MODE, V, NT>(out, row * S + s0, u, live);
         }
     };
-    uint64_t k = 0;
     if constexpr (HasNext8<G>::value) {  // 8 outputs of each stream at a time
-        for (; k + 8 <= count; k += 8) {
+        for (; k + 8 <= end; k += 8) {
             uint32_t d[V][8];
 #pragma unroll
             for (int v = 0; v < V; ++v) g[v].next8(d[v]);
@@ -149,33 +247,37 @@ __global__ __launch_bounds__(kBlock) void k_fill_small(uint8_t *st, uint64_t S, 
             }
         }
     }
-    for (; k < count; ++k) {
+    for (; k < end; ++k) {
         uint32_t u[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) u[v] = g[v].next();
         emit(k, u);
     }
+    if constexpr (!SPLIT) {
 #pragma unroll
-    for (int v = 0; v < V; ++v) g[v].store(st, S, s0 + v);
+        for (int v = 0; v < V; ++v)
+            if (v < live) g[v].store(st, S, s0 + v);
+    }
     if constexpr (MODE == kOutXor) {
         uint32_t *o = static_cast<uint32_t *>(out);
 #pragma unroll
-        for (int v = 0; v < V; ++v) o[s0 + v] = acc[v];
+        for (int v = 0; v < V; ++v)
+            if (v < live) o[s0 + v] = acc[v];
     }
 }
 
 // Small-state kinds, paced: V consecutive streams per thread, BLK threads
-// per workgroup (S % V == 0; threads past the last stream stay in the loop
-// with their stores masked, since they take part in the barriers).
+// per workgroup (threads past the last stream stay in the loop with their
+// stores masked, since they take part in the barriers).
 template <class G, int MODE, int V, int BLK>
 __global__ __launch_bounds__(BLK) void k_fill_paced(uint8_t *st, uint64_t S, uint64_t count, void *out,
                                                     uint32_t *ring) {
     const uint64_t s0 = (static_cast<uint64_t>(blockIdx.x) * BLK + threadIdx.x) * V;
-    const bool live = s0 < S;
+    const uint32_t live = s0 < S ? static_cast<uint32_t>(min(static_cast<uint64_t>(V), S - s0)) : 0;
     G g[V];
 #pragma unroll
     for (int v = 0; v < V; ++v)
-        if (live) g[v].load(st, S, s0 + v);
+        if (v < live) g[v].load(st, S, s0 + v);
     __shared__ uint32_t s_free;
     Pacer pc(ring);
     for (uint64_t k0 = 0, band = 0; k0 < count; k0 += kBand, ++band) {
@@ -184,7 +286,7 @@ __global__ __launch_bounds__(BLK) void k_fill_paced(uint8_t *st, uint64_t S, uin
             uint32_t u[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) u[v] = g[v].next();
-            if (live) store_out<MODE, V>(out, k * S + s0, u);
+            if (live) store_out<MODE, V>(out, k * S + s0, u, live);
         };
         const uint64_t k1 = k0 + kBand < count ? k0 + kBand : count;
         if (k1 - k0 == kBand) {
@@ -198,7 +300,7 @@ __global__ __launch_bounds__(BLK) void k_fill_paced(uint8_t *st, uint64_t S, uin
                     uint32_t u[V];
 #pragma unroll
                     for (int v = 0; v < V; ++v) u[v] = d[v][kk];
-                    if (live) store_out<MODE, V>(out, (k0 + kk) * S + s0, u);
+                    if (live) store_out<MODE, V>(out, (k0 + kk) * S + s0, u, live);
                 }
             } else {
 #pragma unroll
@@ -209,9 +311,9 @@ __global__ __launch_bounds__(BLK) void k_fill_paced(uint8_t *st, uint64_t S, uin
         }
         pc.after(band);
     }
-    if (!live) return;
 #pragma unroll
-    for (int v = 0; v < V; ++v) g[v].store(st, S, s0 + v);
+    for (int v = 0; v < V; ++v)
+        if (v < live) g[v].store(st, S, s0 + v);
 }
 
 // XS1024W: thread t runs lane j = t % 16 of instance g = t / 16.  The output
@@ -367,35 +469,76 @@ void clear_ring(Gen *g, hipStream_t st) {
     hipLaunchKernelGGL(k_zero_ring, dim3((kRing * kPaceSlots + kBlock - 1) / kBlock), dim3(kBlock), 0, st, g->d_ring);
 }
 
+// Unpaced fills.  Streams per thread: one where few streams leave the chip
+// short of waves (a wave's row store is then 256 bytes, but four times as many
+// waves hide the chain of a row: LCG32 FP32 20001 streams x 300, 16 us with
+// four, 8 with one; XORWOW, whose rows cannot be split, 131073 x 500 110 and
+// 80) and for Philox with whole lines in a row, where registers are what holds
+// waves back (2^20 x 1024: 945 and 785); else four (LCG32 99991 x 400 46 with
+// one, 39 with four, 300001 x 1000 571 and 235; Philox 985091 x 266 364 and
+// 290).
+template <class G>
+bool one_stream(uint64_t S) {
+    if (HasNext8<G>::value) return S < 1ull << 16 || S % 32 == 0;
+    return S < (HasAdvance<G>::value ? 1ull << 16 : 1ull << 19);
+}
+// Row blocks: as many as make kSplitWaves waves (two per SIMD), of at least
+// split_rows rows each, about where a block's rows cost as much as the way to
+// its first one: LCG32 1024 x 4096 285 -> 10 us, Philox4x32-10 4096 x 1000 220 ->
+// 11.  (The arrival count is relaxed on purpose: its loads are waited for, and an
+// ordered one writes back the L2 in every workgroup, 33 -> 43 us for Philox4x32-10
+// FP32 99991 x 400.)
+constexpr uint64_t kSplitWaves = 2048, kCached = 256ull << 20;
+template <class G>
+constexpr uint64_t split_rows() {
+    if (HasNext8<G>::value) return 32;
+    if (std::is_same<G, MwcDiff>::value) return 512;  // a power modulo each stream's own p
+    return std::is_same<G, Mwc>::value ? 128 : 64;
+}
+template <class G>
+uint64_t row_blocks(uint64_t waves, uint64_t count) {
+    if (!HasAdvance<G>::value) return 1;
+    return std::max<uint64_t>(1, std::min(kSplitWaves / waves, count / split_rows<G>()));
+}
+
+template <class G, int MODE, int V, bool NT>
+hipError_t fill_free(Gen *g, void *out, uint64_t count, hipStream_t st) {
+    const uint64_t S = g->S;
+    const uint64_t blocks = ((S + V - 1) / V + kBlock - 1) / kBlock;
+    if constexpr (MODE != kOutXor && HasAdvance<G>::value) {
+        const uint64_t by = row_blocks<G>(((S + V - 1) / V + 63) / 64, count);
+        if (by > 1 && g->d_ring && blocks <= kSplitGroups) {
+            const uint64_t rows = ((count + by - 1) / by + 7) / 8 * 8;
+            hipLaunchKernelGGL((k_fill_small<G, MODE, V, true, NT>),
+                               dim3(static_cast<unsigned>(blocks), static_cast<unsigned>((count + rows - 1) / rows)),
+                               dim3(kBlock), 0, st, g->d_state, S, count, out, rows, g->d_ring + kRing * kPaceSlots);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_fill_small<G, MODE, V, false, NT>), dim3(static_cast<unsigned>(blocks)), dim3(kBlock), 0, st,
+                       g->d_state, S, count, out, count, static_cast<uint32_t *>(nullptr));
+    return hipGetLastError();
+}
+
 template <class G, int MODE>
 hipError_t fill_small(Gen *g, void *out, uint64_t count, hipStream_t st) {
     const uint64_t S = g->S;
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
-    const bool vec4 = (S % 4 == 0) && (addr % 16 == 0);
     if constexpr (MODE != kOutXor) {
         const int i = g->fill_cfg >= 0 ? g->fill_cfg : default_config(g->kind);
         const rngx_fill_config c = kSmallConfigs[i];
         const int V = c.streams_per_thread;
-        if (c.paced && S % V == 0 && addr % (4 * V) == 0) {
-            const uint64_t blocks = (S / V + c.block - 1) / c.block;
-            const bool pace = pace_ok(g, i, c, blocks, count);
-            if (pace) clear_ring(g, st);
-            uint32_t *ring = pace ? g->d_ring : nullptr;
-            void *args[] = {&g->d_state, const_cast<uint64_t *>(&S), &count, &out, &ring};
+        const uint64_t blocks = ((S + V - 1) / V + c.block - 1) / c.block;
+        if (c.paced && pace_ok(g, i, c, blocks, count)) {
+            clear_ring(g, st);
+            void *args[] = {&g->d_state, const_cast<uint64_t *>(&S), &count, &out, &g->d_ring};
             const hipError_t e = hipLaunchKernel(config_kernel<G>(MODE, c), dim3(static_cast<unsigned>(blocks)),
                                                  dim3(c.block), args, 0, st);
             return e != hipSuccess ? e : hipGetLastError();
         }
+        if (one_stream<G>(S)) return fill_free<G, MODE, 1, false>(g, out, count, st);
+        if (4 * S * count <= kCached) return fill_free<G, MODE, 4, false>(g, out, count, st);
     }
-    if (vec4) {
-        const uint64_t threads = S / 4;
-        const unsigned blocks = static_cast<unsigned>((threads + kBlock - 1) / kBlock);
-        hipLaunchKernelGGL((k_fill_small<G, MODE, 4>), dim3(blocks), dim3(kBlock), 0, st, g->d_state, S, count, out);
-    } else {
-        const unsigned blocks = static_cast<unsigned>((S + kBlock - 1) / kBlock);
-        hipLaunchKernelGGL((k_fill_small<G, MODE, 1>), dim3(blocks), dim3(kBlock), 0, st, g->d_state, S, count, out);
-    }
-    return hipGetLastError();
+    return fill_free<G, MODE, 4, true>(g, out, count, st);
 }
 
 template <int MODE>
@@ -459,7 +602,9 @@ hipError_t fill_setup(Gen *g, int n_cu) {
     g->n_cu = n_cu;
     g->fill_cfg = -1;
     for (int i = 0; i < kMaxFillConfigs; ++i) g->resident[i] = -1;
-    return hipMalloc(&g->d_ring, 4ull * kRing * kPaceSlots);
+    const size_t bytes = 4ull * (kRing * kPaceSlots + kSplitGroups);  // pacing counters, then k_fill_small's (zero between fills)
+    const hipError_t e = hipMalloc(&g->d_ring, bytes);
+    return e != hipSuccess ? e : hipMemset(g->d_ring, 0, bytes);
 }
 
 int fill_configs(rngx_kind kind, const rngx_fill_config **list) {

@@ -30,6 +30,7 @@ constexpr uint32_t kSlack = 3;        // bands a workgroup may run ahead of the 
 constexpr uint32_t kRing = 32;        // band entries in the counter ring
 constexpr uint32_t kPaceSlots = 256;  // counters per entry (a multiple of 64)
 constexpr uint32_t kPollLimit = 4096; // polls before a workgroup stops waiting
+constexpr uint32_t kSplitGroups = 2048;  // stream groups of a fill in row blocks (see k_fill_small)
 
 enum { kOutU32 = 0, kOutF32 = 1, kOutXor = 2 };
 
@@ -382,9 +383,11 @@ __device__ __forceinline__ void xs1024_apply_poly(const uint32_t *c, uint32_t &a
 #pragma unroll
         for (int i = 31; i >= 0; --i) {
             xs1024_step(a, b);
+            // a ^ (va & m) as one instruction the compiler does not take apart:
+            // else it reorders the xors and the step's last row shifts no longer ride on one
             const uint32_t m = static_cast<uint32_t>(static_cast<int32_t>(word << (31 - i)) >> 31);
-            a ^= va & m;
-            b ^= vb & m;
+            a = __builtin_amdgcn_bitop3_b32(a, va, m, 0x78);
+            b = __builtin_amdgcn_bitop3_b32(b, vb, m, 0x78);
         }
     }
 }

@@ -489,3 +489,25 @@ def test_substream_lcg_state_header_is_checked(rngx, orc):
         with pytest.raises(rngx.RngxError):
             rngx.rng_set_state(g, bad)
         assert np.array_equal(rngx.rng_get_state(g), other)
+
+
+@pytest.mark.parametrize("kind", ["lcg32", "lcg64", "mwc", "philox4x32_10", "philox4x32_7", "lcg32_sub", "lcg64_sub",
+                                  "mwc_diff", "xorwow"])
+def test_fill_row_blocks(rngx, orc, kind):
+    """Fills of few streams and many rows are cut into row blocks (counts on
+    both sides of where that begins and not multiples of a block), stream
+    counts that leave a thread's last streams unused and rows unaligned; each
+    fill goes on from the one before."""
+    for S in (1, 6, 255, 1001, 4100):
+        g = rngx.rng_create(kind, S, 9)
+        st = orc.seed(kind, S, 9)
+        for i, count in enumerate((255, 256, 301, 2051, 3)):
+            print(f"case row blocks {kind} S={S} count={count}", flush=True)
+            f32 = i % 2 == 1
+            out = torch.empty(S * count + 4, dtype=torch.float32 if f32 else torch.int32, device="cuda").fill_(7)
+            (rngx.rng_fill_f32 if f32 else rngx.rng_fill_u32)(g, out, count)
+            want = orc.generate(kind, S, st, count, mode=orc.OUT_F32 if f32 else orc.OUT_U32)
+            got = out.cpu().numpy()
+            assert np.all(got[S * count:] == 7), (kind, S, count)
+            assert np.array_equal(got[:S * count].view(want.dtype).reshape(count, S), want), (kind, S, count)
+            assert np.array_equal(rngx.rng_get_state(g), st), (kind, S, count)
