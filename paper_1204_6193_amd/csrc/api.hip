@@ -674,14 +674,33 @@ rngx_status rng_set_state(rngx_gen h, const void *host_buf, size_t bytes, void *
     return RNGX_OK;
 }
 
+static void free_tiles(Ising *lat) {
+    (void)hipFree(lat->alt_spins);
+    (void)hipFree(lat->alt_state);
+    lat->alt_spins = nullptr;
+    lat->alt_state = nullptr;
+}
+
 static void free_ising(Ising *lat) {
     (void)hipFree(lat->d_spins);
     (void)hipFree(lat->d_halo);
     (void)hipFree(lat->d_err);
     (void)hipFree(lat->d_partial);
+    free_tiles(lat);
     free_gen(lat->gen);
     lat->magic = 0;
     delete lat;
+}
+
+// Second images of the spins and states for tiled sweeps.  Where they don't
+// fit, the lattice sweeps per pass.
+static void alloc_tiles(Ising *lat) {
+    if (lat->plan.strips || lat->alt_state || !ising_tiled(lat)) return;
+    hipError_t e = hipMalloc(&lat->alt_spins, static_cast<size_t>(lat->L) * lat->L);
+    if (e == hipSuccess) e = hipMalloc(&lat->alt_state, lat->gen->state_bytes);
+    if (e == hipSuccess) return;
+    (void)hipGetLastError();
+    free_tiles(lat);
 }
 
 rngx_status ising_create(uint32_t L, rngx_kind kind, uint64_t seed, rngx_ising *out) {
@@ -716,6 +735,7 @@ rngx_status ising_create(uint32_t L, rngx_kind kind, uint64_t seed, rngx_ising *
         free_ising(lat);
         return fail(RNGX_E_NOMEM, "device allocation for the lattice failed");
     }
+    alloc_tiles(lat);
     e = launch_seed(g, seed, nullptr);
     if (e == hipSuccess) e = launch_hot_start(lat, seed, nullptr);
     if (e == hipSuccess) e = launch_zero(lat->d_err, 1, nullptr);
@@ -784,6 +804,8 @@ hipError_t apply_plan(Ising *lat, const IsingPlan &p) {
     if (e != hipSuccess) return e;
     lat->plan = p;
     lat->epoch = 0;
+    if (p.strips) free_tiles(lat);
+    alloc_tiles(lat);
     return hipSuccess;
 }
 

@@ -901,8 +901,146 @@ const void *bits_kernel_for(rngx_kind kind, uint32_t slots, bool hits, bool gang
     return nullptr;
 }
 
+// VALU instructions of one slot's draws in a colour pass, comparisons and
+// shifts into the outcome words included (counted in the compiled loops), and
+// of a pass beside its draws.
+int bits_slot_cost(rngx_kind kind) {
+    switch (kind) {
+    case RNGX_XS1024W: return 50;
+    case RNGX_PHILOX4X32_10: return 36;
+    case RNGX_PHILOX4X32_7: return 28;
+    case RNGX_XORWOW: return 24;
+    case RNGX_LCG64:
+    case RNGX_LCG64_SUB: return 18;
+    default: return 12;
+    }
+}
+constexpr int kBitsPassCost = 80;
+
+template <class Unit> struct KindOf { static constexpr rngx_kind kind = static_cast<rngx_kind>(0); };
+template <> struct KindOf<SmallUnit<Lcg32>> { static constexpr rngx_kind kind = RNGX_LCG32; };
+template <> struct KindOf<SmallUnit<Lcg32Sub>> { static constexpr rngx_kind kind = RNGX_LCG32_SUB; };
+template <> struct KindOf<SmallUnit<Lcg64>> { static constexpr rngx_kind kind = RNGX_LCG64; };
+template <> struct KindOf<SmallUnit<Lcg64Sub>> { static constexpr rngx_kind kind = RNGX_LCG64_SUB; };
+template <> struct KindOf<SmallUnit<Mwc>> { static constexpr rngx_kind kind = RNGX_MWC; };
+template <> struct KindOf<SmallUnit<MwcDiff>> { static constexpr rngx_kind kind = RNGX_MWC_DIFF; };
+template <> struct KindOf<SmallUnit<Xorwow>> { static constexpr rngx_kind kind = RNGX_XORWOW; };
+template <> struct KindOf<PhiloxUnit> { static constexpr rngx_kind kind = RNGX_PHILOX4X32_10; };
+template <> struct KindOf<PhiloxUnit7> { static constexpr rngx_kind kind = RNGX_PHILOX4X32_7; };
+template <> struct KindOf<XsUnit> { static constexpr rngx_kind kind = RNGX_XS1024W; };
+
+// ---- tiled sweeps of a lattice without strips
+constexpr double kTileBytesPerPs = 4.4, kTileInstrPerPs = 39.3;  // a large copy's rate; VALU lane instructions
+const void *tiles_kernel_for(rngx_kind kind, bool hits) {
+    switch (kind) {
+    case RNGX_LCG32:
+    case RNGX_LCG64:
+    case RNGX_MWC: return tiles_kernel_lcg(kind, hits);
+    case RNGX_LCG32_SUB:
+    case RNGX_LCG64_SUB: return tiles_kernel_own(kind, hits);
+    case RNGX_PHILOX4X32_10:
+    case RNGX_PHILOX4X32_7: return tiles_kernel_philox(kind, hits);
+    case RNGX_XORWOW:
+    case RNGX_XS1024W: return tiles_kernel_xorshift(kind, hits);
+    default: return nullptr;  // MWC_DIFF holds a multiplier per stream, a lagged Fibonacci instance 1024 units
+    }
+}
+
+// Tile of a kind whose units hold NB sites: threads, rows side by side, and
+// sites per row.  Two workgroups of 512 threads or more share a CU, so that
+// one loads while the other sweeps; XS1024W takes 1024 columns, since 256 of
+// them are margin.
+struct TileShape {
+    uint32_t threads, VB, w, h, grain;  // grain: columns the margin is a multiple of
+};
+template <int NB>
+TileShape tile_shape() {
+    constexpr uint32_t threads = NB == 4 ? 512 : 1024, w = NB == 4 ? 256 : 1024;
+    constexpr uint32_t VB = threads / (w / NB);
+    return {threads, VB, w, VB * (64 / NB), NB == 4 ? 4u : 128u};
+}
+
+// Sweeps of n per block of tiles: an even number of blocks, so that the last
+// one writes the images the lattice is held in, of the size with the least
+// time by the bytes it moves and the instructions it issues, margins included
+// (the two overlap for the most part; 16 MWC sweeps at L = 8192: 380 us by
+// this, 437 measured).
+template <class Unit>
+uint32_t tile_sweeps(const Ising *lat, uint64_t n, uint32_t hits) {
+    constexpr int NB = Unit::kNB;
+    const TileShape ts = tile_shape<NB>();
+    const rngx_kind kind = lat->gen->kind;
+    const double bytes = 1.0 + static_cast<double>(lat->gen->state_bytes) / (static_cast<double>(lat->L) * lat->L);
+    const double valu = 2.0 * (static_cast<double>(bits_slot_cost(kind)) * hits + kBitsPassCost * NB / 64.0) / NB;
+    double best = 1e300;
+    uint32_t s_best = 1;
+    for (uint32_t s = 1; s <= 8; ++s) {
+        const uint64_t blocks = 2 * ((n + 2 * s - 1) / (2 * s));
+        const uint32_t my = 2 * s, mx = (my + ts.grain - 1) / ts.grain * ts.grain;
+        const double eff = static_cast<double>(ts.w - 2 * mx) / ts.w * (ts.h - 2 * my) / ts.h;
+        const double mem = static_cast<double>(blocks) * bytes * (1 + 1 / eff) / kTileBytesPerPs;
+        const double alu = static_cast<double>(n) * valu / eff / kTileInstrPerPs;
+        const double cost = std::max(mem, alu) + std::min(mem, alu) / 4;
+        if (cost < best) {
+            best = cost;
+            s_best = s;
+        }
+    }
+    return s_best;
+}
+
+template <class Unit, bool MH>
+hipError_t run_tiles(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t *tr, hipStream_t st, uint32_t hits) {
+    constexpr int NB = Unit::kNB;
+    const TileShape ts = tile_shape<NB>();
+    const uint32_t L = lat->L, s_max = tile_sweeps<Unit>(lat, n, hits);
+    const uint64_t blocks = 2 * ((n + 2 * s_max - 1) / (2 * s_max));
+    const void *fn = tiles_kernel_for(lat->gen->kind, MH);
+    const uint32_t lds = bits_lds_bytes(lat->gen->kind, ts.threads, 64 / NB);
+    if (tr)
+        hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<unsigned>((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
+                           reinterpret_cast<uint32_t *>(tr), n);
+    TileArgs a{};
+    a.s.S = lat->gen->S;
+    a.s.L = L;
+    a.s.R = ts.h;
+    a.s.nwg = 1;
+    a.s.T4 = T4;
+    a.s.T8 = T8;
+    a.s.hits = hits;
+    a.s.VB = ts.VB;
+    a.s.cst = lat->gen->d_state;
+    a.s.tile_w = ts.w;
+    for (uint64_t b = 0, done = 0; b < blocks; ++b) {
+        a.s.n_sweeps = n / blocks + (b < n % blocks ? 1 : 0);
+        a.s.spins = b & 1 ? lat->alt_spins : lat->d_spins;
+        a.s.st = b & 1 ? lat->alt_state : lat->gen->d_state;
+        a.s.spins_out = b & 1 ? lat->d_spins : lat->alt_spins;
+        a.s.st_out = b & 1 ? lat->gen->d_state : lat->alt_state;
+        a.s.trace = tr ? tr + done : nullptr;
+        a.margin_y = 2 * static_cast<uint32_t>(a.s.n_sweeps);
+        a.margin_x = (a.margin_y + ts.grain - 1) / ts.grain * ts.grain;
+        a.keep_w = ts.w - 2 * a.margin_x;
+        a.keep_h = ts.h - 2 * a.margin_y;
+        a.tiles_x = (L + a.keep_w - 1) / a.keep_w;
+        const uint32_t tiles = a.tiles_x * ((L + a.keep_h - 1) / a.keep_h);
+        void *args[] = {&a};
+        const hipError_t e = hipLaunchKernel(fn, dim3(tiles), dim3(ts.threads), args, lds, st);
+        if (e != hipSuccess) return e;
+        done += a.s.n_sweeps;
+    }
+    return hipGetLastError();
+}
+
 template <class Unit, bool MH>
 hipError_t run_passes(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t *tr, hipStream_t st, uint32_t hits) {
+    // One sweep cannot end in the images it starts from.  XS1024W multi-hit
+    // sweeps are bound by their draws, which the margin of whole instances
+    // makes 1.8 times as many (8 sweeps of 4 hits at L = 8192: 213 us a sweep
+    // in tiles, 183 per pass; the other kinds gain at any hits, Philox 4x32-10
+    // 313 -> 202).
+    if constexpr (!std::is_same<Unit, SmallUnit<MwcDiff>>::value && !(MH && std::is_same<Unit, XsUnit>::value))
+        if (lat->alt_state && n >= 2) return run_tiles<Unit, MH>(lat, T4, T8, n, tr, st, hits);
     constexpr int NB = Unit::kNB;
     const uint64_t L = lat->L, n_units = L * L / NB;
     const unsigned blocks = static_cast<unsigned>((n_units + kBlock - 1) / kBlock);
@@ -956,22 +1094,6 @@ hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
     return hipGetLastError();
 }
 
-// VALU instructions of one slot's draws in a colour pass, comparisons and
-// shifts into the outcome words included (counted in the compiled loops), and
-// of a pass beside its draws.
-int bits_slot_cost(rngx_kind kind) {
-    switch (kind) {
-    case RNGX_XS1024W: return 50;
-    case RNGX_PHILOX4X32_10: return 36;
-    case RNGX_PHILOX4X32_7: return 28;
-    case RNGX_XORWOW: return 24;
-    case RNGX_LCG64:
-    case RNGX_LCG64_SUB: return 18;
-    default: return 12;
-    }
-}
-constexpr int kBitsPassCost = 80;
-
 // Rows side by side (VB) and slots per thread of a strip of R rows whose
 // spins are bits; the strip's neighbours have R rows too, or fewer at the
 // lattice's end.  nt = VB L / NB threads hold units; XS1024W needs nt to be a
@@ -1022,18 +1144,6 @@ bool try_bits(uint32_t L, rngx_kind kind, uint32_t NB, int n_cu, IsingPlan *p) {
     }
     return true;
 }
-
-template <class Unit> struct KindOf { static constexpr rngx_kind kind = static_cast<rngx_kind>(0); };
-template <> struct KindOf<SmallUnit<Lcg32>> { static constexpr rngx_kind kind = RNGX_LCG32; };
-template <> struct KindOf<SmallUnit<Lcg32Sub>> { static constexpr rngx_kind kind = RNGX_LCG32_SUB; };
-template <> struct KindOf<SmallUnit<Lcg64>> { static constexpr rngx_kind kind = RNGX_LCG64; };
-template <> struct KindOf<SmallUnit<Lcg64Sub>> { static constexpr rngx_kind kind = RNGX_LCG64_SUB; };
-template <> struct KindOf<SmallUnit<Mwc>> { static constexpr rngx_kind kind = RNGX_MWC; };
-template <> struct KindOf<SmallUnit<MwcDiff>> { static constexpr rngx_kind kind = RNGX_MWC_DIFF; };
-template <> struct KindOf<SmallUnit<Xorwow>> { static constexpr rngx_kind kind = RNGX_XORWOW; };
-template <> struct KindOf<PhiloxUnit> { static constexpr rngx_kind kind = RNGX_PHILOX4X32_10; };
-template <> struct KindOf<PhiloxUnit7> { static constexpr rngx_kind kind = RNGX_PHILOX4X32_7; };
-template <> struct KindOf<XsUnit> { static constexpr rngx_kind kind = RNGX_XS1024W; };
 
 // Try one decomposition into nwg strips; fills *out if it fits on chip.
 template <class Unit>
@@ -1411,6 +1521,21 @@ int ising_plan_list(uint32_t L, rngx_kind kind, int n_cu, IsingPlan *out, int ma
     default: break;
     }
     return 0;
+}
+
+// A tile has to fit the lattice once; XS1024W instances (128 sites) lie within
+// a row where L is a multiple of 128.
+bool ising_tiled(const Ising *lat) {
+    const rngx_kind kind = lat->gen->kind;
+    const bool xs = kind == RNGX_XS1024W;
+    const TileShape ts = xs ? tile_shape<8>() : tile_shape<4>();
+    if (lat->L < ts.w || lat->L < ts.h || (xs && lat->L % 128)) return false;
+    for (bool hits : {false, true}) {
+        if (hits && xs) continue;
+        const void *fn = tiles_kernel_for(kind, hits);
+        if (!fn || blocks_per_cu(fn, ts.threads, bits_lds_bytes(kind, ts.threads, xs ? 8 : 16)) < 1) return false;
+    }
+    return true;
 }
 
 bool ising_plan(uint32_t L, rngx_kind kind, int n_cu, IsingPlan *out) {

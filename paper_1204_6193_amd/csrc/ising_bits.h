@@ -111,8 +111,11 @@ template <class Unit> struct IsPhiloxKey : std::false_type {};
 template <int ROUNDS> struct IsPhiloxKey<PhiloxKeyUnitR<ROUNDS>> : std::true_type {};
 
 // All sweeps of strip r (R rows at row r R0) by the calling workgroup.
-// GANG: several strips (else the strip is the lattice).
-template <class Unit, int SPT, bool MH, bool GANG>
+// GANG: several strips (else the strip is the lattice).  TILE: a tile of a
+// lattice in memory (k_ising_tiles), which wraps on itself instead of asking
+// its neighbours and keeps only what lies farther from its edges than the
+// passes it makes.
+template <class Unit, int SPT, bool MH, bool GANG, bool TILE = false>
 __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32_t *lds) {
     constexpr int NB = Unit::kNB, G = NB / 2;
     constexpr uint32_t kGroup = 16 / G;  // lanes that share a halo word
@@ -122,7 +125,7 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
     constexpr uint32_t kEvenSlots = G == 2 ? 0x33333333u : 0x0F0F0F0Fu;
     static_assert(SPT * G <= 32, "a colour's sites are one word");
     const uint32_t t = threadIdx.x;
-    const uint32_t L = a.L, R = a.R, VB = a.VB, nwg = GANG ? a.nwg : 1, upr = L / NB, nt = VB * upr;
+    const uint32_t L = a.L, R = a.R, VB = a.VB, nwg = GANG ? a.nwg : 1, upr = (TILE ? a.tile_w : L) / NB, nt = VB * upr;
     const uint32_t nth = (nt + 63) / 64 * 64;  // threads of the waves that hold units
     if (t >= nth) {  // whole waves of a wider workgroup (a batch's): the barriers below, nothing else
         for (uint64_t n = 2 * a.n_sweeps; n; --n) __syncthreads();
@@ -130,11 +133,35 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
         if (a.trace && a.n_sweeps > 0) __syncthreads();
         return;
     }
-    const uint64_t row0 = static_cast<uint64_t>(r) * a.R0;
-    const bool active = t < nt;
+    const uint64_t row0 = TILE ? a.y0 : static_cast<uint64_t>(r) * a.R0;
+    const bool active = TILE || t < nt;
     const uint32_t vb = active ? t / upr : 0, col = active ? t - vb * upr : 0;
-    const uint32_t rows = active && vb < R ? (R - 1 - vb) / VB + 1 : 0;  // of this thread
-    const uint32_t own = rows * G >= 32 ? ~0u : (1u << (rows * G)) - 1;
+    // of this thread (a tile fills its workgroup, so all its loads can be in flight at once)
+    const uint32_t rows = TILE ? SPT : active && vb < R ? (R - 1 - vb) / VB + 1 : 0;
+    // the sites the energies count: the thread's own, of a tile those it keeps
+    uint32_t own = rows * G >= 32 ? ~0u : (1u << (rows * G)) - 1;
+    uint32_t counted = rows;
+    if constexpr (TILE) {
+        own = counted = 0;
+        if (col - a.in_x < a.n_x)
+            for (uint32_t i = 0; i < rows; ++i)
+                if (vb + i * VB - a.in_y < a.n_y) {
+                    own |= GM << (G * i);
+                    ++counted;
+                }
+    }
+    const uint32_t row_units = L / NB;
+    // lattice row of slot i, and a thread's unit in that row
+    auto row_of = [&](uint32_t vb_, int i) -> uint64_t {
+        const uint64_t y = row0 + vb_ + static_cast<uint64_t>(i) * VB;
+        return TILE && y >= L ? y - L : y;
+    };
+    auto unit_of = [&](uint32_t col_) -> uint32_t {
+        if constexpr (!TILE) return col_;
+        const uint32_t c = a.x0 / NB + col_;
+        return c >= row_units ? c - row_units : c;
+    };
+    const uint32_t ucol = unit_of(col);
     // slots whose row is even
     const uint32_t flat = VB & 1 ? kEvenSlots : ~0u;
     const uint32_t even = (row0 + vb) & 1 ? ~flat : flat;
@@ -165,7 +192,7 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
         b[1] = (o | (o >> 15)) & 3;
     };
     auto row_bits = [&](uint64_t y, uint32_t (&b)[2]) {  // colour bits of the thread's unit in row y
-        const uint32_t *p = reinterpret_cast<const uint32_t *>(a.spins + y * L + static_cast<uint64_t>(col) * NB);
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(a.spins + y * L + static_cast<uint64_t>(ucol) * NB);
         uint32_t q[2];
         colours(p[0], q);
         if constexpr (NB == 8) {
@@ -178,19 +205,23 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
         b[1] = y & 1 ? q[0] : q[1];
     };
     const uint64_t ubase = row0 * upr;
+    constexpr bool kHasCst = std::is_same<Unit, PhiloxUnit>::value || std::is_same<Unit, PhiloxUnit7>::value ||
+                             std::is_same<Unit, XsUnit>::value;  // image parts that no update changes
     constexpr bool kSub = !std::is_void<typename SubWord<Unit>::type>::value;
     LcgMap<std::conditional_t<kSub, typename SubWord<Unit>::type, uint32_t>> map{};
-    if constexpr (kSub) map = Unit::map(a.st, a.S);
+    if constexpr (kSub) map = Unit::map(TILE ? a.cst : a.st, a.S);
     Unit u[SPT];
 #pragma unroll
     for (int i = 0; i < SPT; ++i) {
         u[i] = Unit{};
         if (static_cast<uint32_t>(i) < rows) {
-            const uint64_t k = ubase + t + static_cast<uint64_t>(i) * nt;
+            const uint64_t k = TILE ? row_of(vb, i) * row_units + ucol : ubase + t + static_cast<uint64_t>(i) * nt;
             if constexpr (kWeylLds) u[i].load(a.st, a.S, k, weyl0 + i);
+            else if constexpr (TILE && kHasCst) u[i].load(a.st, a.cst, a.S, k);
+            else if constexpr (TILE && IsPhiloxKey<Unit>::value) u[i].load(a.cst, a.S, k);
             else u[i].load(a.st, a.S, k);
             uint32_t b[2];
-            row_bits(row0 + vb + static_cast<uint64_t>(i) * VB, b);
+            row_bits(row_of(vb, i), b);
             W[0] |= b[0] << (G * i);
             W[1] |= b[1] << (G * i);
         }
@@ -297,14 +328,14 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
     // every second pass: stores and loads complete in order.)
     uint32_t unlike = 0;  // differing neighbours of the thread's colour-1 sites
     auto reduce_energy = [&](uint64_t sweep) {
-        const int v = wave_sum_last(static_cast<int>(4 * G * rows) - 2 * static_cast<int>(unlike));
+        const int v = wave_sum_last(static_cast<int>(4 * G * counted) - 2 * static_cast<int>(unlike));
         if ((t & 63) == 63) atomicAdd(&e_ring[sweep % kBitsRing], v);
     };
     auto flush_energy = [&](uint64_t first, uint32_t n) {
         for (uint32_t i = t; i < n; i += nth) {
             const int v = e_ring[i];
             e_ring[i] = 0;
-            if constexpr (GANG) atomicAdd(a.trace + first + i, -v);
+            if constexpr (GANG || TILE) atomicAdd(a.trace + first + i, -v);
             else a.trace[first + i] = -v;  // the only contributor
         }
     };
@@ -532,22 +563,29 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
         const uint32_t e = (even_bits | even_bits << 15) & 0x00010001u, o = (odd_bits | odd_bits << 15) & 0x00010001u;
         return ((e | o << 8) * 0xFEu) ^ 0x01010101u;
     };
+    const uint32_t ucol2 = unit_of(col2);
+    int8_t *const spins_out = TILE ? a.spins_out : a.spins;
+    uint8_t *const st_out = TILE ? a.st_out : a.st;
 #pragma unroll
     for (int i = 0; i < SPT; ++i) {
-        if (static_cast<uint32_t>(i) < rows2) {
-            const uint64_t y = row0 + vb2 + static_cast<uint64_t>(i) * VB;
+        bool keep = static_cast<uint32_t>(i) < rows2;
+        if constexpr (TILE) keep = keep && col2 - a.in_x < a.n_x && vb2 + i * VB - a.in_y < a.n_y;
+        if (keep) {
+            const uint64_t y = row_of(vb2, i);
             const uint32_t b0 = (W[0] >> (G * i)) & GM, b1 = (W[1] >> (G * i)) & GM;
             const uint32_t e = y & 1 ? b1 : b0, o = y & 1 ? b0 : b1;
-            uint32_t *p = reinterpret_cast<uint32_t *>(a.spins + y * L + static_cast<uint64_t>(col2) * NB);
+            uint32_t *p = reinterpret_cast<uint32_t *>(spins_out + y * L + static_cast<uint64_t>(ucol2) * NB);
             p[0] = bytes(e & 3, o & 3);
             if constexpr (NB == 8) p[1] = bytes(e >> 2, o >> 2);
-            const uint64_t k = ubase + t2 + static_cast<uint64_t>(i) * nt;
+            const uint64_t k = TILE ? y * row_units + ucol2 : ubase + t2 + static_cast<uint64_t>(i) * nt;
+            const uint64_t steps = 4 * a.n_sweeps * (MH ? a.hits : 1);
             if constexpr (IsPhiloxKey<Unit>::value)
-                u[i].put_position(a.st, a.S, k, MH ? a.blk0 + 4ull * a.n_sweeps * a.hits : 4 * (a.blk0 + a.n_sweeps));
+                u[i].put_position(st_out, a.S, k, MH ? a.blk0 + steps : 4 * (a.blk0 + a.n_sweeps));
             else if constexpr (kWeylLds)
-                u[i].store(a.st, a.S, k, weyl0[i] + static_cast<uint32_t>(4 * a.n_sweeps * (MH ? a.hits : 1)) * kWeylC);
-            else if constexpr (SweepCounter<Unit>::value) u[i].store_at(a.st, a.S, k, a);
-            else u[i].store(a.st, a.S, k, 4 * a.n_sweeps * (MH ? a.hits : 1));
+                u[i].store(st_out, a.S, k, weyl0[i] + static_cast<uint32_t>(steps) * kWeylC);
+            else if constexpr (SweepCounter<Unit>::value) u[i].store_at(st_out, a.S, k, a);
+            else if constexpr (TILE && std::is_same<Unit, XsUnit>::value) u[i].store(st_out, a.st, a.S, k, steps);
+            else u[i].store(st_out, a.S, k, steps);
         }
     }
 }
@@ -608,6 +646,90 @@ template <class Unit>
 const void *bits_kernel_of(int slots, bool hits, bool gang) {
     if (gang) return hits ? bits_kernel_of<Unit, true, true>(slots) : bits_kernel_of<Unit, false, true>(slots);
     return hits ? bits_kernel_of<Unit, true, false>(slots) : bits_kernel_of<Unit, false, false>(slots);
+}
+
+// A lattice that does not fit on chip, a few sweeps at a time: each workgroup
+// takes a tile with `margin` rows and columns around the part it keeps, makes
+// 2 n_sweeps <= margin passes on chip (the margin's sites are updated like all
+// others, from their own streams, and turn wrong from the edge inwards one site
+// a pass) and writes what it keeps, spins and states, to another image; the
+// next block of sweeps goes back.  One launch per colour pass moves every
+// state and spin twice per sweep and is bound by that; a block moves them once
+// per n_sweeps and the margins once more, and its loads, all in flight at
+// once, overlap the passes of the CU's other workgroups.  L = 8192, us per
+// sweep of 8, per pass -> tiles: MWC 153 -> 35 (bytes 25, instructions 18),
+// LCG32 126 -> 29, XORWOW 366 -> 89, Philox 4x32-10 226 -> 65, XS1024W
+// 131 -> 68 (its margin of whole instances, 128 columns, costs 1.8 times the
+// instructions).
+// Tiles in the order of the lattice within each of the 8 dies.
+__device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t n) {
+    const uint32_t q = n / 8, rest = n % 8, x = b % 8;
+    return x * q + min(x, rest) + b / 8;
+}
+
+template <class Unit, bool MH>
+__global__ __launch_bounds__(kBitsMaxThreads) void k_ising_tiles(TileArgs ta) {
+    constexpr int NB = Unit::kNB, SPT = 64 / NB;
+    extern __shared__ __align__(16) uint32_t bits_lds[];
+    StripArgs a = ta.s;
+    const uint32_t tile = xcd_order(blockIdx.x, gridDim.x), tx = tile % ta.tiles_x, ty = tile / ta.tiles_x, L = a.L;
+    const uint32_t kx = tx * ta.keep_w, ky = ty * ta.keep_h;  // the kept part's place in the lattice
+    a.x0 = kx >= ta.margin_x ? kx - ta.margin_x : kx + L - ta.margin_x;
+    a.y0 = ky >= ta.margin_y ? ky - ta.margin_y : ky + L - ta.margin_y;
+    a.in_x = ta.margin_x / NB;
+    a.in_y = ta.margin_y;
+    a.n_x = min(ta.keep_w, L - kx) / NB;
+    a.n_y = min(ta.keep_h, L - ky);
+    // the tile's units, for the tests of what its streams share
+    const uint32_t upr = a.tile_w / NB, row_units = L / NB, x0u = a.x0 / NB;
+    auto all_equal = [&](auto &&value, uint64_t *first) {
+        const uint32_t vb = threadIdx.x / upr;
+        uint32_t x = x0u + threadIdx.x % upr;
+        if (x >= row_units) x -= row_units;
+        *first = value(static_cast<uint64_t>(a.y0) * row_units + x0u);
+        uint64_t v[SPT];
+#pragma unroll
+        for (int i = 0; i < SPT; ++i) {
+            uint32_t y = a.y0 + vb + i * a.VB;
+            if (y >= L) y -= L;
+            v[i] = value(static_cast<uint64_t>(y) * row_units + x);
+        }
+        int ok = 1;
+#pragma unroll
+        for (int i = 0; i < SPT; ++i) ok &= v[i] == *first;
+        return __syncthreads_and(ok) != 0;
+    };
+    if constexpr (std::is_same<Unit, PhiloxUnit>::value || std::is_same<Unit, PhiloxUnit7>::value) {
+        using Key = PhiloxKeyUnitR<std::is_same<Unit, PhiloxUnit>::value ? 10 : 7>;
+        const uint64_t *pos = reinterpret_cast<const uint64_t *>(a.st + 8 * a.S);
+        uint64_t p;
+        if (all_equal([&](uint64_t u) { return pos[u]; }, &p) && (MH || (p & 3) == 0)) {
+            a.blk0 = MH ? p : p >> 2;
+            bits_body<Key, SPT, MH, false, true>(a, 0, bits_lds);
+            return;
+        }
+    }
+    if constexpr (std::is_same<Unit, XsUnit>::value && !MH) {
+        const uint64_t *N = reinterpret_cast<const uint64_t *>(a.st + 4 * a.S);
+        uint64_t n;
+        if (all_equal([&](uint64_t u) { return N[u >> 4]; }, &n)) {
+            a.blk0 = n;
+            a.y_start = *reinterpret_cast<const uint32_t *>(a.cst + 4 * a.S + 8 * (a.S / 32)) + static_cast<uint32_t>(n) * kWeylC;
+            bits_body<XsSweepUnit, SPT, false, false, true>(a, 0, bits_lds);
+            return;
+        }
+    }
+    if constexpr (std::is_same<Unit, SmallUnit<Xorwow>>::value) bits_body<XorwowStripUnit, SPT, MH, false, true>(a, 0, bits_lds);
+    else if constexpr (std::is_same<Unit, SmallUnit<Lcg32Sub>>::value) bits_body<LcgSubStripUnit<uint32_t>, SPT, MH, false, true>(a, 0, bits_lds);
+    else if constexpr (std::is_same<Unit, SmallUnit<Lcg64Sub>>::value) bits_body<LcgSubStripUnit<uint64_t>, SPT, MH, false, true>(a, 0, bits_lds);
+    else bits_body<Unit, SPT, MH, false, true>(a, 0, bits_lds);
+}
+
+template <class Unit>
+const void *tiles_kernel_of(bool hits) {
+    if constexpr (!std::is_same<Unit, XsUnit>::value)
+        if (hits) return reinterpret_cast<const void *>(&k_ising_tiles<Unit, true>);
+    return hits ? nullptr : reinterpret_cast<const void *>(&k_ising_tiles<Unit, false>);
 }
 
 // Batches whose replicas all keep their spins as bits (or stream through

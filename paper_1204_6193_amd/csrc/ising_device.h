@@ -43,6 +43,12 @@ struct PhiloxUnitR {
         k0 = p[u]; k1 = p[S + u];
         pos = reinterpret_cast<const uint64_t *>(st + 8 * S)[u];
     }
+    // keys from the image `cst`
+    __device__ void load(const uint8_t *st, const uint8_t *cst, uint64_t S, uint64_t u) {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(cst);
+        k0 = p[u]; k1 = p[S + u];
+        pos = reinterpret_cast<const uint64_t *>(st + 8 * S)[u];
+    }
     __device__ void store(uint8_t *st, uint64_t S, uint64_t u, uint64_t) const {
         reinterpret_cast<uint64_t *>(st + 8 * S)[u] = pos;
     }
@@ -219,9 +225,22 @@ struct XsUnit {
         const uint64_t n = reinterpret_cast<const uint64_t *>(st + 4 * S)[u >> 4];
         y = *reinterpret_cast<const uint32_t *>(st + 4 * S + 8 * (S / 32)) + static_cast<uint32_t>(n) * kWeylC;
     }
+    // the Weyl seed from the image `cst`
+    __device__ void load(const uint8_t *st, const uint8_t *cst, uint64_t S, uint64_t u) {
+        const uint2 w = reinterpret_cast<const uint2 *>(st)[u];
+        a = w.x; b = w.y;
+        const uint64_t n = reinterpret_cast<const uint64_t *>(st + 4 * S)[u >> 4];
+        y = *reinterpret_cast<const uint32_t *>(cst + 4 * S + 8 * (S / 32)) + static_cast<uint32_t>(n) * kWeylC;
+    }
     __device__ void store(uint8_t *st, uint64_t S, uint64_t u, uint64_t steps) const {
         reinterpret_cast<uint2 *>(st)[u] = make_uint2(a, b);
         if ((u & 15) == 0) reinterpret_cast<uint64_t *>(st + 4 * S)[u >> 4] += steps;
+    }
+    // to another image than the one loaded from
+    __device__ void store(uint8_t *st, const uint8_t *from, uint64_t S, uint64_t u, uint64_t steps) const {
+        reinterpret_cast<uint2 *>(st)[u] = make_uint2(a, b);
+        if ((u & 15) == 0)
+            reinterpret_cast<uint64_t *>(st + 4 * S)[u >> 4] = reinterpret_cast<const uint64_t *>(from + 4 * S)[u >> 4] + steps;
     }
     __device__ void draw(uint32_t (&r)[4]) {
         xs1024_step(a, b);
@@ -292,6 +311,20 @@ struct StripArgs {
     uint64_t blk0;              // sweep forms, at the start: Philox the common block index, XS1024W the step count
     uint32_t y_start;           // sweep-form XS1024W: the common Weyl word at the start
     uint32_t VB;                // spins as bits: rows side by side in a workgroup (slot i of a thread is row vb + i VB)
+    // tiles (k_ising_tiles): the images the tile writes, and the one with what no update changes
+    int8_t *spins_out;
+    uint8_t *st_out;
+    const uint8_t *cst;
+    uint32_t tile_w, x0, y0;    // sites a tile's row holds; its first site (the tile wraps at the lattice's edge)
+    uint32_t in_x, in_y;        // first column (in units) and row of the part the tile keeps
+    uint32_t n_x, n_y;          // and its units per row and rows
+};
+
+// A tiled block of sweeps.
+struct TileArgs {
+    StripArgs s;
+    uint32_t tiles_x, keep_w, keep_h, margin_x;  // of all tiles: kept sites per row and rows, columns before them
+    uint32_t margin_y;
 };
 
 // LDS of a strip whose spins are bits: two words a thread, a zero, and the

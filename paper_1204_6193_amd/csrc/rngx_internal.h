@@ -98,6 +98,8 @@ struct Ising {
     uint32_t halo_nwg;   // strips the halo allocation is sized for
     uint32_t *d_err;     // strips: set if a neighbour wait gave up
     int32_t *d_partial;  // per-pass path: per-block energy partials
+    int8_t *alt_spins;   // tiled sweeps: the images every second block writes (null where sweeps run per pass)
+    uint8_t *alt_state;
     uint64_t epoch;      // passes run since the halo tags were last cleared
     uint32_t batches;    // batches that hold this lattice
 };
@@ -208,6 +210,12 @@ const void *batch_bits_kernel_lcg(rngx_kind kind, uint32_t threads);
 const void *batch_bits_kernel_own(rngx_kind kind, uint32_t threads);
 const void *batch_bits_kernel_philox(rngx_kind kind, uint32_t threads);
 const void *batch_bits_kernel_xorshift(rngx_kind kind, uint32_t threads);
+// Kernels that sweep tiles of a lattice in memory.
+const void *tiles_kernel_lcg(rngx_kind kind, bool hits);
+const void *tiles_kernel_own(rngx_kind kind, bool hits);
+const void *tiles_kernel_philox(rngx_kind kind, bool hits);
+const void *tiles_kernel_xorshift(rngx_kind kind, bool hits);
+bool ising_tiled(const Ising *lat);  // whether a lattice without strips sweeps in tiles
 bool ising_plan(uint32_t L, rngx_kind kind, int n_cu, IsingPlan *out);
 int ising_plan_list(uint32_t L, rngx_kind kind, int n_cu, IsingPlan *out, int max);  // strip candidates
 // Plans b (shape b->shape) from b->lats, b->betas, b->traces and `sweeps`
