@@ -64,19 +64,25 @@ rngx_status ragged_fill_noalloc(Gen *g, const uint64_t *offsets, uint64_t units,
         return fail(RNGX_E_OVERFLOW, "the request list needs about " + std::to_string(bound) +
                                          " chunks, more than the 64 MiB scratch holds");
     RaggedPlan plan;
-    ragged_plan(g->kind, offsets, units, g->n_cu, &plan);
     const std::vector<RaggedItem> &items = plan.items;
-    if (items.empty()) return RNGX_OK;
     std::vector<uint64_t> t64, lane;
     std::vector<uint32_t> t32;
-    jump_table_gen(g, plan.step, plan.max_j + 1, &t64, &t32);
     if (ragged_lane_table(g->kind)) ragged_lane_maps(g, &lane);
     // layout: items | chunk states | t64 | t32 | lane maps | slots
-    const size_t b_items = up(sizeof(RaggedItem) * items.size());
-    const size_t b_state = up(ragged_scratch_bytes(g->kind, items.size()));
-    const size_t b_t64 = up(8 * t64.size()), b_t32 = up(4 * t32.size());
-    const size_t b_lane = up(8 * lane.size()), b_slots = up(4 * plan.slots.size());
-    const size_t need = b_items + b_state + b_t64 + b_t32 + b_lane + b_slots;
+    size_t b_items, b_state, b_t64, b_t32, b_lane, b_slots, need;
+    for (bool few_slots : {false, true}) {  // XS1024W: the plan with fewer slots may still fit
+        ragged_plan(g->kind, offsets, units, g->n_cu, &plan, 0, few_slots);
+        if (items.empty()) return RNGX_OK;
+        jump_table_gen(g, plan.step, plan.max_j + 1, &t64, &t32);
+        b_items = up(sizeof(RaggedItem) * items.size());
+        b_state = up(ragged_scratch_bytes(g->kind, items.size()));
+        b_t64 = up(8 * t64.size());
+        b_t32 = up(4 * t32.size());
+        b_lane = up(8 * lane.size());
+        b_slots = up(4 * plan.slots.size());
+        need = b_items + b_state + b_t64 + b_t32 + b_lane + b_slots;
+        if (need <= kScratchBytes || g->kind != RNGX_XS1024W) break;
+    }
     if (need > kScratchBytes)
         return fail(RNGX_E_OVERFLOW, "the request list needs " + std::to_string(need) +
                                          " bytes of staging, more than the 64 MiB scratch");

@@ -18,6 +18,7 @@
 // 16-lane row generates all chunks of its slot in turn, so no row waits on a
 // longer one and the only jumps are those at the cuts.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <vector>
 
@@ -403,19 +404,24 @@ __global__ __launch_bounds__(kBlock) void k_ragged_start_small(rngx_kind kind, c
 // second kernel copies it back, so no row can read a state another row has
 // already advanced.
 //
-// Stores are aligned to 32-word (128-byte) output lines: step k's 32 words
-// go into a 64-word LDS ring and lane i writes the word pair at positions
-// 2i, 2i+1 of line k of the chunk's aligned span, which holds the last `mis`
-// words of step k-1 and the first 32-mis of step k (mis: the chunk's start
-// modulo 32 words).  Inside a chunk every store is one whole line per row;
-// only the first and last lines of a chunk are partial.
+// Two steps make a span of 64 words, and stores are aligned to such spans of
+// the output (256 bytes): the words of pair k go into a 128-word LDS ring and
+// lane i writes the four words at positions 4i .. 4i + 3 of span k, which
+// holds the last `mis` words of pair k-1 and the first 64-mis of pair k (mis:
+// the chunk's start modulo 64 words).  Inside a chunk every store is one whole
+// span per row; only the first and last spans of a chunk are partial.  25
+// vector instructions a step (about 0.65 ms for 2e9 words on the whole card)
+// run beside the stores (1.13 ms at a plain fill's rate); the jumps at the
+// start, 1024 steps each, do not.  2e9 words with spans of one step and 8-byte
+// stores 1764 us, with spans of two 1674.
+constexpr uint32_t kXsRing = 288;  // words from row to row
 __global__ __launch_bounds__(kBlock) void k_ragged_xs(const RaggedItem *items, uint64_t n_items,
                                                        const uint32_t *slots, uint32_t n_slots, const uint8_t *st,
                                                        uint64_t S, const uint32_t *t32, uint64_t chunk,
                                                        uint8_t *scratch, uint32_t *out) {
-    // 64-word ring per row, kept twice (word p at p and p + 64) so that a
-    // lane's pair never wraps
-    __shared__ uint32_t ring[kBlock / 16][128];
+    // 128-word ring per row, kept twice (word p at p and p + 128) so that a
+    // lane's four words never wrap
+    __shared__ uint32_t ring[kBlock / 16][kXsRing];
     const uint64_t t = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     const uint64_t r = t >> 4;
     const uint32_t lane = static_cast<uint32_t>(t & 15), rl = threadIdx.x >> 4;
@@ -429,11 +435,10 @@ __global__ __launch_bounds__(kBlock) void k_ragged_xs(const RaggedItem *items, u
     // the wave would run every chunk index as long as its longest row.
     uint32_t q = slots[r];
     RaggedItem it;
-    uint32_t a, b, y, mis, len, kf, k;
-    // ring positions of the lane's pair: written (step k's words 2 lane, 2
-    // lane + 1 at 32 k mod 64) and read (line k at 32 k + 2 lane - mis mod 64),
-    // for the current parity of k; xor with *_flip moves to the other parity
-    uint32_t wcur, rcur, wflip, rflip;
+    uint32_t a, b, y, mis, len, kf, k, pairs;
+    // ring positions: the lane's words of pair k's first step (64 k + 2 lane
+    // mod 128) and its words of span k (64 k + 4 lane - mis mod 128)
+    uint32_t wcur, rcur;
     uint64_t n;
     int64_t nvals;
     uint32_t *o;
@@ -448,31 +453,46 @@ __global__ __launch_bounds__(kBlock) void k_ragged_xs(const RaggedItem *items, u
             n += it.j * chunk;
         }
         y = y0 + static_cast<uint32_t>(n) * kWeylC;
-        mis = static_cast<uint32_t>(out_word + it.out) & 31;
-        o = out + (it.out - mis) + 2 * lane;  // lane's pair in line 0 (positions < mis unused)
+        mis = static_cast<uint32_t>(out_word + it.out) & 63;
+        o = out + (it.out - mis) + 4 * lane;  // lane's words of span 0 (positions < mis unused)
         len = it.len;
+        pairs = (len + 1) / 2;
         nvals = static_cast<int64_t>(it.nvals);
-        // lines 1 .. kf are whole: 32 k - mis >= 0 and 32 k + 32 - mis <= nvals
-        const int64_t kf_ = (nvals + mis - 32) / 32;
-        kf = kf_ <= 0 ? 0 : static_cast<uint32_t>(min(kf_, static_cast<int64_t>(len) - 1));
+        // spans 1 .. kf are whole and made of whole pairs
+        const int64_t kf_ = min((nvals + mis - 64) / 64, static_cast<int64_t>(len / 2) - 1);
+        kf = kf_ <= 0 ? 0 : static_cast<uint32_t>(kf_);
         k = 0;
         wcur = 2 * lane;
-        wflip = 32;
-        rcur = (2 * lane - mis) & 63;
-        rflip = rcur ^ ((32 + 2 * lane - mis) & 63);
+        rcur = (4 * lane - mis) & 127;
         // Loads complete here: stores share the memory counter, so a wait
         // left to the step loop would also wait for the stores.
         __builtin_amdgcn_s_waitcnt(0x0F70);
     };
+    auto step = [&](uint32_t at) {  // one step into the ring
+        xs1024_step(a, b);
+        y += kWeylC;
+        const uint32_t m = weyl_mix(y);
+        const uint2 pv = make_uint2(a + m, b + m);
+        *reinterpret_cast<uint2 *>(rg + at) = pv;
+        *reinterpret_cast<uint2 *>(rg + at + 128) = pv;
+    };
+    auto span = [&]() {  // the lane's words of span k
+        __builtin_amdgcn_wave_barrier();
+        const u32x4 v = {rg[rcur], rg[rcur + 1], rg[rcur + 2], rg[rcur + 3]};
+        __builtin_amdgcn_wave_barrier();
+        wcur ^= 64;
+        rcur ^= 64;
+        return v;
+    };
     begin();
     while (true) {
-        if (k == len) {
-            {  // line len: the last mis words of step len-1
-                const uint32_t f0 = rg[rcur], f1 = rg[rcur + 1];
-                __builtin_amdgcn_wave_barrier();
-                const int64_t v0 = 32 * static_cast<int64_t>(len) + 2 * lane - mis;
-                if (v0 < nvals) o[0] = f0;
-                if (v0 + 1 < nvals) o[1] = f1;
+        if (k == pairs) {
+            {  // span `pairs`: the last mis words of the last pair
+                const u32x4 f = span();
+                const int64_t v0 = 64 * static_cast<int64_t>(pairs) + 4 * lane - mis;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (v0 + j < nvals) o[j] = f[j];
             }
             if (it.last) {
                 reinterpret_cast<uint2 *>(scratch)[16ull * q + lane] = make_uint2(a, b);
@@ -481,46 +501,31 @@ __global__ __launch_bounds__(kBlock) void k_ragged_xs(const RaggedItem *items, u
             if (++q == q_end) break;
             begin();
         }
-        if (k >= 1 && k + 3 <= kf) {  // lines k .. k+3 whole: four steps with no tests
+        if (k >= 1 && k + 1 <= kf) {  // spans k, k+1 whole: four steps with no tests
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                xs1024_step(a, b);
-                y += kWeylC;
-                const uint32_t m = weyl_mix(y);
-                const uint2 pv = make_uint2(a + m, b + m);
-                *reinterpret_cast<uint2 *>(rg + wcur) = pv;
-                *reinterpret_cast<uint2 *>(rg + wcur + 64) = pv;
-                __builtin_amdgcn_wave_barrier();
-                const uint32_t w0 = rg[rcur], w1 = rg[rcur + 1];
-                __builtin_amdgcn_wave_barrier();
-                wcur ^= wflip;
-                rcur ^= rflip;
-                __builtin_nontemporal_store(w0 | static_cast<uint64_t>(w1) << 32, reinterpret_cast<uint64_t *>(o + 32 * j));
+            for (int j = 0; j < 2; ++j) {
+                step(wcur);
+                step(wcur + 32);
+                __builtin_nontemporal_store(span(), reinterpret_cast<u32x4 *>(o + 64 * j));
             }
             o += 128;
-            k += 4;
-            continue;  // k <= kf + 1 <= len: the chunk may end here
+            k += 2;
+            continue;  // k <= kf + 1 <= pairs: the chunk may end here
         }
-        // step k into the ring, then the lane's pair of line k
-        xs1024_step(a, b);
-        y += kWeylC;
-        const uint32_t m = weyl_mix(y);
-        const uint2 pv = make_uint2(a + m, b + m);
-        *reinterpret_cast<uint2 *>(rg + wcur) = pv;
-        *reinterpret_cast<uint2 *>(rg + wcur + 64) = pv;
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t w0 = rg[rcur], w1 = rg[rcur + 1];
-        __builtin_amdgcn_wave_barrier();
-        wcur ^= wflip;
-        rcur ^= rflip;
-        if (k - 1 < kf) {  // 1 <= k <= kf: a whole line
-            __builtin_nontemporal_store(w0 | static_cast<uint64_t>(w1) << 32, reinterpret_cast<uint64_t *>(o));
+        // pair k into the ring (a chunk of odd length ends on half a pair),
+        // then the lane's words of span k
+        step(wcur);
+        if (2 * k + 1 < len) step(wcur + 32);
+        const u32x4 v = span();
+        if (k - 1 < kf) {  // 1 <= k <= kf: a whole span
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(o));
         } else {
-            const int64_t v0 = 32 * static_cast<int64_t>(k) + 2 * lane - mis;
-            if (v0 >= 0 && v0 < nvals) o[0] = w0;
-            if (v0 + 1 >= 0 && v0 + 1 < nvals) o[1] = w1;
+            const int64_t v0 = 64 * static_cast<int64_t>(k) + 4 * lane - mis;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (v0 + j >= 0 && v0 + j < nvals) o[j] = v[j];
         }
-        o += 32;
+        o += 64;
         ++k;
     }
 }
@@ -801,7 +806,22 @@ uint64_t ragged_shape_value(rngx_kind kind, int shape) {
 
 uint64_t ragged_chunk(rngx_kind kind, int shape) { return ragged_shape_value(kind, shape); }
 
-void ragged_plan(rngx_kind kind, const uint64_t *off, uint64_t n_units, int n_cu, RaggedPlan *plan, int shape) {
+// Rows for T XS1024W steps on n_cu CUs.  A step takes a row 0.12 us, a jump 45
+// us whatever the slot's length, and R rows' jumps 0.012 R us of the device:
+// 0.12 T / R + 0.012 R is least at sqrt(T / 10) steps a row.  Beyond a
+// workgroup per CU the rows fill whole rounds of workgroups (12e6 steps on
+// 8480 rows: 460 us, on 8192 or 12288: 385-397).  With 2048 steps or more a
+// row at any T, 4000 requests of up to 2000 words took 480 us (now 57), one of
+// 3e6 words 240 (107), 6000 of up to 65536 words 301 (241) and 4000 of up to
+// 10^6 1674 (1650).
+uint64_t xs_rows(uint64_t T, uint64_t n_cu) {
+    const uint64_t steps = std::max<uint64_t>(128, static_cast<uint64_t>(std::sqrt(static_cast<double>(T) / 10)));
+    const uint64_t rows = (T + steps - 1) / steps, round = kBlock / 16 * n_cu;
+    return rows <= round ? rows : (rows + round / 2) / round * round;
+}
+
+void ragged_plan(rngx_kind kind, const uint64_t *off, uint64_t n_units, int n_cu, RaggedPlan *plan, int shape,
+                 bool few_slots) {
     std::vector<RaggedItem> &items = plan->items;
     items.clear();
     plan->slots.clear();
@@ -839,9 +859,12 @@ void ragged_plan(rngx_kind kind, const uint64_t *off, uint64_t n_units, int n_cu
     while ((max_steps + J - 1) / J > 16384) J *= 2;
     plan->step = J;
     if (T == 0) return;
-    const uint64_t R = std::max<uint64_t>(
-        1, std::min<uint64_t>(ragged_shape_value(kind, shape) * std::max(n_cu, 1), (T + kXsMinSlotSteps - 1) / kXsMinSlotSteps));
+    const uint64_t cus = static_cast<uint64_t>(std::max(n_cu, 1));
+    const uint64_t rows = few_slots ? (T + kXsFewSlotSteps - 1) / kXsFewSlotSteps : xs_rows(T, cus);
+    const uint64_t R = std::max<uint64_t>(1, std::min<uint64_t>(ragged_shape_value(kind, shape) * cus, rows));
     const uint64_t Q = (T + R - 1) / R;
+    // a jump takes as long as 400 steps: short slots run an instance's last 512 steps on
+    const uint64_t run_on = Q < 512 ? 512 : 0;
     // Slot r should end at (r + 1) Q placed steps; G (steps placed) stays
     // below the open slot's target between pieces.
     uint64_t G = 0, r = 0;
@@ -856,7 +879,7 @@ void ragged_plan(rngx_kind kind, const uint64_t *off, uint64_t n_units, int n_cu
             if (G + (steps - p) >= target) {  // the slot ends in this instance
                 close = true;
                 const uint64_t want = p + (target - G);
-                if (want < steps) {
+                if (want + run_on < steps) {
                     uint64_t cut = (want + J / 2) / J * J;
                     if (cut <= p) cut = p + J;
                     if (cut < steps) end = cut;

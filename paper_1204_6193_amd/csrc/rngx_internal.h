@@ -235,7 +235,7 @@ struct RaggedPlan {
     uint64_t step = 1, max_j = 0;
 };
 constexpr uint32_t kXsRowsPerCu = 128;      // most rows per CU of any shape: 8 waves per SIMD x 4 SIMDs x 4 rows
-constexpr uint64_t kXsMinSlotSteps = 2048;  // slots are not cut finer than this
+constexpr uint64_t kXsFewSlotSteps = 2048;  // fewest steps of a slot where the plan has to be small
 // Shapes of a ragged plan, tuned per plan: XS1024W generating rows per CU,
 // other kinds outputs per chunk.  Shape 0 is the default.
 constexpr int kRaggedShapes = 3;
@@ -244,7 +244,8 @@ uint64_t ragged_chunk(rngx_kind kind, int shape = 0);
 bool ragged_affine(rngx_kind kind);  // LCG32/LCG64 and sub-stream forms: one wave per chunk
 bool ragged_wave(rngx_kind kind);    // affine kinds, MWC, MWC_DIFF, Philox: one wave per chunk, 1 KiB spans
 bool ragged_lane_table(rngx_kind kind);  // kinds whose wave kernel takes lane_maps (ragged_lane_maps)
-void ragged_plan(rngx_kind kind, const uint64_t *off, uint64_t n_units, int n_cu, RaggedPlan *plan, int shape = 0);
+void ragged_plan(rngx_kind kind, const uint64_t *off, uint64_t n_units, int n_cu, RaggedPlan *plan, int shape = 0,
+                 bool few_slots = false);
 size_t ragged_scratch_bytes(rngx_kind kind, uint64_t n_items);
 void ragged_lane_maps(const Gen *g, std::vector<uint64_t> *lane);  // affine kinds: lane start and advance maps
 // The one-call ragged fill of rng_fill_ragged_u32_noalloc (noalloc.hip):

@@ -225,3 +225,26 @@ def test_ragged_bench_shape_sampled(rngx, orc, kind, shape):
     assert np.array_equal(rngx.rng_get_state(g), st), kind
     del out
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("shift", [0, 1, 31, 32, 33, 63])
+def test_ragged_xs_spans_and_cuts(rngx, orc, shift):
+    """XS1024W: chunk ends and starts around the 64-word spans of the stores
+    and around half a pair of steps, output views at any word, and requests
+    long and short enough for slots cut inside instances and not."""
+    lens = [63, 64, 65, 1, 31, 32, 33, 95, 96, 97, 127, 128, 129, 191, 193, 0, 255, 257, 32 * 127, 32 * 128 + 1,
+            32 * 129 - 1, 32 * 700 + 5, 32 * 1000, 32 * 5000 + 17, 7]
+    S = 32 * len(lens)
+    g = rngx.rng_create("xs1024w", S, 21)
+    st = orc.seed("xs1024w", S, 21)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
+    plan = rngx.rng_ragged_create(g, off)
+    for call in range(2):
+        print(f"case ragged spans shift={shift} call={call}", flush=True)
+        buf = torch.full((int(off[-1]) + 80,), -1, dtype=torch.int32, device="cuda")
+        rngx.rng_fill_ragged_u32(plan, buf[shift:])
+        got = buf.cpu().numpy().view(np.uint32)
+        want = _oracle_ragged(orc, "xs1024w", S, st, lens)
+        assert np.array_equal(got[shift:shift + int(off[-1])], want)
+        assert np.all(got[:shift] == 0xFFFFFFFF) and np.all(got[shift + int(off[-1]):] == 0xFFFFFFFF)
+        assert np.array_equal(rngx.rng_get_state(g), st)
