@@ -537,6 +537,13 @@ hipError_t fill_small(Gen *g, void *out, uint64_t count, hipStream_t st) {
         }
         if (one_stream<G>(S)) return fill_free<G, MODE, 1, false>(g, out, count, st);
         if (4 * S * count <= kCached) return fill_free<G, MODE, 4, false>(g, out, count, st);
+    } else if (S < 1ull << 19 || (S % 4 && S < 1ull << 21)) {
+        // Nothing to store: four times the waves hide a stream's chain of steps
+        // (512 rows, four streams a thread and one: LCG32 2^12 streams 22 and 13
+        // us, 2^18 36 and 18, 2^19 30 and 30, 2^20 45 and 51; MWC 2^18 29 and 21),
+        // and of the sizes that fill no whole round of workgroups the smaller
+        // ones lose less (Philox4x32-10 2^19 + 1 130 and 85).
+        return fill_free<G, MODE, 1, false>(g, out, count, st);
     }
     return fill_free<G, MODE, 4, true>(g, out, count, st);
 }
