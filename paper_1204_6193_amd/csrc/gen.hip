@@ -185,11 +185,11 @@ __global__ __launch_bounds__(kBlock) void k_fill_small(uint8_t *st, uint64_t S, 
                                                        uint64_t rows, uint32_t *arrived) {
     const uint64_t s0 = (static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * V;
     if (!SPLIT && s0 >= S) return;
-    const uint32_t live = s0 < S ? static_cast<uint32_t>(min(static_cast<uint64_t>(V), S - s0)) : 0;
+    const uint32_t live = V == 1 && !SPLIT ? 1 : s0 < S ? static_cast<uint32_t>(min(static_cast<uint64_t>(V), S - s0)) : 0;
     G g[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        g[v] = G{};
+        if constexpr (V > 1 || SPLIT) g[v] = G{};
         if (v < live) g[v].load(st, S, s0 + v);
     }
     uint64_t k = 0, end = count;
