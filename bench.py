@@ -39,7 +39,8 @@ STATE_BYTES = {"lcg32": 4, "lcg64": 8, "mwc": 8, "xorwow": 24, "philox4x32_10": 
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "xs1024w_fill_u32_2p20x4096_hbm_traffic.md")
 PROFILE_ISING_VALU = os.path.join(ROOT, "profiles", "ising_valu_L4096_all_kinds.md")
 KERNEL_SOURCES = ["paper_1204_6193_amd/csrc/gen.hip", "paper_1204_6193_amd/csrc/rngx_device.h"]
-ISING_SOURCES = ["paper_1204_6193_amd/csrc/ising.hip", "paper_1204_6193_amd/csrc/rngx_device.h"]
+ISING_SOURCES = ["paper_1204_6193_amd/csrc/" + f for f in
+                 ("ising.hip", "ising_bits.h", "ising_device.h", "ising_memory.h", "rngx_device.h")]
 # VALU issue peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (a wave64 instruction
 # occupies a SIMD for 4 cycles)
 VALU_PEAK_LANE_INSTR = 256 * 4 * 16 * 2.4e9

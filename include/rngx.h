@@ -233,11 +233,13 @@ rngx_status rng_autotune_fill(rngx_gen g, uint32_t *d_out, uint64_t count_per_st
 
 /* Ising plans and their autotuner.  A lattice runs either as strips held on
  * chip by cooperating workgroups (one per strip; the strip count is the
- * sub-lattice tiling) or, if no strip plan fits, one launch per colour pass.
- * Every plan gives the same spins, energies and stream states.
+ * sub-lattice tiling) or, if no strip plan fits, from memory: two or more
+ * sweeps in tiles that make a few sweeps per pass over memory (between the
+ * lattice and a second image, which takes the lattice's size again), else one
+ * launch per colour pass.  Every plan gives the same spins, energies and stream states.
  * ising_plans: the strip counts that fit this lattice, most strips first,
- * then 0 (the per-pass path); strips_out (n entries) may be NULL to ask for
- * *n only.  ising_set_plan: use `strips` strips (0: per pass); synchronizes
+ * then 0 (from memory); strips_out (n entries) may be NULL to ask for
+ * *n only.  ising_set_plan: use `strips` strips (0: from memory); synchronizes
  * the device.  ising_autotune: times every plan on `reps` (>= 1) calls of
  * n_sweeps sweeps at beta after one warm-up call, keeps the fastest and
  * restores the spins and stream states it started from (saved to device
@@ -359,8 +361,8 @@ rngx_status ising_sweep_hits(rngx_ising lat, double beta, uint64_t n_sweeps, uin
 
 /* How the lattice is swept: *strips receives the number of workgroups that
  * hold the lattice on chip as horizontal strips for a whole ising_sweep call
- * (1 = a single workgroup), or 0 when every colour pass is a separate launch
- * that streams spins and state through memory (large L).  Results do not
+ * (1 = a single workgroup), or 0 when spins and state are streamed through
+ * memory (large L).  Results do not
  * depend on it.  Any output pointer may be NULL. */
 rngx_status ising_info(rngx_ising lat, uint32_t *L, rngx_kind *kind, uint32_t *strips);
 

@@ -609,9 +609,9 @@ hipError_t fill_setup(Gen *g, int n_cu) {
     g->n_cu = n_cu;
     g->fill_cfg = -1;
     for (int i = 0; i < kMaxFillConfigs; ++i) g->resident[i] = -1;
-    const size_t bytes = 4ull * (kRing * kPaceSlots + kSplitGroups);  // pacing counters, then k_fill_small's (zero between fills)
-    const hipError_t e = hipMalloc(&g->d_ring, bytes);
-    return e != hipSuccess ? e : hipMemset(g->d_ring, 0, bytes);
+    // pacing counters (each paced fill clears them), then k_fill_small's (zero between fills)
+    const hipError_t e = hipMalloc(&g->d_ring, 4ull * (kRing * kPaceSlots + kSplitGroups));
+    return e != hipSuccess ? e : launch_zero(g->d_ring + kRing * kPaceSlots, kSplitGroups, nullptr);
 }
 
 int fill_configs(rngx_kind kind, const rngx_fill_config **list) {
