@@ -476,7 +476,9 @@ void clear_ring(Gen *g, hipStream_t st) {
 // 80) and for Philox with whole lines in a row, where registers are what holds
 // waves back (2^20 x 1024: 945 and 785); else four (LCG32 99991 x 400 46 with
 // one, 39 with four, 300001 x 1000 571 and 235; Philox 985091 x 266 364 and
-// 290).
+// 290).  Short fills take one as well, whatever the streams: up to 2^23 values
+// (LCG32 100002 x 64 14 us with four, 7 with one, 300001 x 32 11 and 12; Philox
+// 1032178 x 4 13 and 8), XORWOW 2^24 (1032178 x 8 23 and 14).
 template <class G>
 bool one_stream(uint64_t S) {
     if (HasNext8<G>::value) return S < 1ull << 16 || S % 32 == 0;
@@ -536,7 +538,13 @@ hipError_t fill_small(Gen *g, void *out, uint64_t count, hipStream_t st) {
             return e != hipSuccess ? e : hipGetLastError();
         }
         if (one_stream<G>(S)) return fill_free<G, MODE, 1, false>(g, out, count, st);
-        if (4 * S * count <= kCached) return fill_free<G, MODE, 4, false>(g, out, count, st);
+        // (XORWOW's states fill the L2 themselves: 1032178 x 4 11.3 us with plain stores, 9.7 without)
+        if (S * count < (HasAdvance<G>::value ? 1ull << 23 : 1ull << 24))
+            return fill_free<G, MODE, 1, !HasAdvance<G>::value>(g, out, count, st);
+        // Rows that are not made of whole vectors meet in a line, which the L2
+        // puts together; aligned ones don't need it (2^20 x 16 14.2 and 12.8 us).
+        const bool aligned = S % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
+        if (!aligned && 4 * S * count <= kCached) return fill_free<G, MODE, 4, false>(g, out, count, st);
     } else if (S < 1ull << 19 || (S % 4 && S < 1ull << 21)) {
         // Nothing to store: four times the waves hide a stream's chain of steps
         // (512 rows, four streams a thread and one: LCG32 2^12 streams 22 and 13
