@@ -596,6 +596,10 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
 // all alike, take what they share from the call's start.
 template <class Unit, int SPT, bool MH, bool GANG>
 __device__ __forceinline__ void bits_strip(const StripArgs &a, uint32_t r, uint32_t *lds) {
+    // A batch's replica may have no sweeps: nothing moves.  (Its body makes the
+    // first pass's draws before it enters the loop over the sweeps; testing there
+    // took 2% of a lone strip's pass.)
+    if (a.n_sweeps == 0) return;
     StripArgs b = a;
     if constexpr (std::is_same<Unit, PhiloxUnit>::value || std::is_same<Unit, PhiloxUnit7>::value) {
         using Key = PhiloxKeyUnitR<std::is_same<Unit, PhiloxUnit>::value ? 10 : 7>;

@@ -126,3 +126,36 @@ def test_batch_sizes(rngx, orc, kind):
             assert np.array_equal(traces[i].cpu().numpy(), want), (shape, Ls[i])
             assert np.array_equal(rngx.ising_get_spins(lats[i]).ravel(), sp), (shape, Ls[i])
             assert np.array_equal(rngx.rng_get_state(rngx.ising_rng(lats[i])), st), (shape, Ls[i])
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_batch_replicas_without_sweeps(rngx, orc, kind):
+    """Replicas of zero sweeps among others, lone workgroups and gangs, their
+    streams at one position and apart: such a replica's spins and streams stay
+    as they are."""
+    Ls = [48, 64, 256, 784, 784, 112, 64]
+    sweeps = [0, 3, 0, 0, 2, 2, 0]
+    lats = [rngx.ising_create(L, kind, 90 + i) for i, L in enumerate(Ls)]
+    refs = [orc.ising_create(L, kind, 90 + i) for i, L in enumerate(Ls)]
+    if kind.startswith("philox") or kind == "xs1024w":  # the last replica's streams at positions of their own
+        S = Ls[-1] ** 2 // 4
+        st = np.array(refs[-1][1], dtype=np.uint8)
+        at, n = (4 * S, S // 32) if kind == "xs1024w" else (8 * S, S)
+        st[at:at + 8 * n] = np.random.default_rng(2).integers(0, 1000, n).astype(np.uint64).view(np.uint8)
+        rngx.rng_set_state(rngx.ising_rng(lats[-1]), st)
+        refs[-1] = (refs[-1][0], st)
+    traces = [torch.full((max(n, 1),), 7, dtype=torch.int32, device="cuda") for n in sweeps]
+    batch = rngx.ising_batch_create(lats, [0.42] * len(Ls), sweeps, traces)
+    for shape in (0, 4):
+        print(f"case bits batch without sweeps {kind} shape={shape}", flush=True)
+        rngx.ising_batch_set_shape(batch, shape)
+        rngx.ising_batch_run(batch)
+        assert rngx.ising_batch_status(batch) == 0
+        for i, (sp, st) in enumerate(refs):
+            if sweeps[i]:
+                want = orc.ising_sweeps(Ls[i], kind, 0.42, st, sp, sweeps[i])
+                assert np.array_equal(traces[i].cpu().numpy(), want), (shape, i)
+            else:
+                assert int(traces[i][0]) == 7, (shape, i)
+            assert np.array_equal(rngx.ising_get_spins(lats[i]).ravel(), sp), (shape, i, Ls[i])
+            assert np.array_equal(rngx.rng_get_state(rngx.ising_rng(lats[i])), st), (shape, i, Ls[i])
