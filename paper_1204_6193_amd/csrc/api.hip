@@ -693,7 +693,8 @@ static void free_ising(Ising *lat) {
 }
 
 // Second images of the spins and states for tiled sweeps.  Where they don't
-// fit, the lattice sweeps per pass.
+// fit, the lattice sweeps per pass.  Once there they live as long as the
+// lattice, under any later plan: a graph captured from tiled sweeps holds them.
 static void alloc_tiles(Ising *lat) {
     if (lat->plan.strips || lat->alt_state || !ising_tiled(lat)) return;
     hipError_t e = hipMalloc(&lat->alt_spins, static_cast<size_t>(lat->L) * lat->L);
@@ -804,7 +805,6 @@ hipError_t apply_plan(Ising *lat, const IsingPlan &p) {
     if (e != hipSuccess) return e;
     lat->plan = p;
     lat->epoch = 0;
-    if (p.strips) free_tiles(lat);
     alloc_tiles(lat);
     return hipSuccess;
 }
@@ -856,6 +856,7 @@ rngx_status ising_autotune(rngx_ising h, double beta, uint64_t n_sweeps, int32_t
     const int k = plan_candidates(lat, list);
     list[k] = IsingPlan{};  // the per-pass path
     const size_t sbytes = static_cast<size_t>(lat->L) * lat->L, gbytes = lat->gen->state_bytes;
+    const bool had_tiles = lat->alt_state != nullptr;
     void *saved_spins = nullptr, *saved_state = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipMalloc(&saved_spins, sbytes);
@@ -894,6 +895,7 @@ rngx_status ising_autotune(rngx_ising h, double beta, uint64_t n_sweeps, int32_t
     if (e == hipSuccess) e = apply_plan(lat, list[best]);
     if (e == hipSuccess) e = hipMemcpy(lat->d_spins, saved_spins, sbytes, hipMemcpyDeviceToDevice);
     if (e == hipSuccess) e = hipMemcpy(lat->gen->d_state, saved_state, gbytes, hipMemcpyDeviceToDevice);
+    if (e == hipSuccess && !had_tiles && lat->plan.strips) free_tiles(lat);  // only this call's runs used them
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     (void)hipFree(saved_spins);

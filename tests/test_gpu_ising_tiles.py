@@ -114,3 +114,42 @@ def test_tiles_in_a_graph(rngx, kind):
             _sweep(rngx, b, 0.4, 1, 1, tb[i:i + 1])
         assert torch.equal(ta, tb)
         _same(rngx, a, b)
+
+
+@pytest.mark.parametrize("kind", ["mwc", "xs1024w"])
+def test_graph_of_tiles_outlives_its_plan(rngx, orc, kind):
+    """A graph captured from tiled sweeps goes on giving the oracle's lattice
+    after the lattice was moved to strips and after it was tuned, and writes to
+    nothing but the lattice's own memory."""
+    L = 1024 if kind == "xs1024w" else 512
+    lat = _lattice(rngx, L, kind)
+    sp, st = orc.ising_create(L, kind, 5)
+    tr = torch.zeros(4, dtype=torch.int32, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        rngx.ising_sweep(lat, 0.4, 4, tr)
+
+    def check(n, got):
+        want = orc.ising_sweeps(L, kind, 0.4, st, sp, n)
+        assert np.array_equal(got.cpu().numpy(), want)
+        assert np.array_equal(rngx.ising_get_spins(lat).ravel(), sp)
+        assert np.array_equal(rngx.rng_get_state(rngx.ising_rng(lat)), st)
+
+    plans = [p for p in rngx.ising_plans(lat) if p]
+    for step in ("memory", "strips", "tuned"):
+        print(f"case tiles graph after {step} {kind}", flush=True)
+        if step == "strips":
+            rngx.ising_set_plan(lat, plans[0])
+        elif step == "tuned":
+            rngx.ising_autotune(lat, 0.4, 2, reps=1)
+        torch.cuda.empty_cache()
+        other = [torch.full((L * L * b // 4,), 7, dtype=torch.int32, device="cuda") for b in (1, 1, 2, 2)]
+        t2 = torch.zeros(3, dtype=torch.int32, device="cuda")
+        rngx.ising_sweep(lat, 0.4, 3, t2)
+        check(3, t2)
+        for _ in range(2):
+            g.replay()
+            torch.cuda.synchronize()
+            check(4, tr)
+        assert all(bool((t == 7).all()) for t in other)
