@@ -976,6 +976,7 @@ uint32_t tile_sweeps(const Ising *lat, uint64_t n, uint32_t hits) {
     uint32_t s_best = 1;
     for (uint32_t s = 1; s <= 8; ++s) {
         const uint64_t blocks = 2 * ((n + 2 * s - 1) / (2 * s));
+        if (blocks > n) continue;  // every block makes a sweep (s = 2 always fits)
         const uint32_t my = 2 * s, mx = (my + ts.grain - 1) / ts.grain * ts.grain;
         const double eff = static_cast<double>(ts.w - 2 * mx) / ts.w * (ts.h - 2 * my) / ts.h;
         const double mem = static_cast<double>(blocks) * bytes * (1 + 1 / eff) / kTileBytesPerPs;

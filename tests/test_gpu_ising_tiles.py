@@ -7,6 +7,8 @@ import numpy as np
 import pytest
 import torch
 
+import hipgraph
+
 pytestmark = pytest.mark.gpu
 
 KINDS = ["lcg32", "lcg64", "mwc", "lcg32_sub", "lcg64_sub", "xorwow", "philox4x32_10", "philox4x32_7", "xs1024w"]
@@ -153,3 +155,23 @@ def test_graph_of_tiles_outlives_its_plan(rngx, orc, kind):
             torch.cuda.synchronize()
             check(4, tr)
         assert all(bool((t == 7).all()) for t in other)
+
+
+@pytest.mark.parametrize("kind", ["lcg32", "xorwow", "philox4x32_7"])
+@pytest.mark.parametrize("n", [3, 5])
+def test_every_tile_block_sweeps(rngx, orc, kind, n):
+    """An odd number of sweeps with many hits, which would take one sweep a
+    block: no block without a sweep is launched, and the lattice is the
+    oracle's."""
+    L, hits = 272, 100
+    lat = _lattice(rngx, L, kind)
+    sp, st = orc.ising_create(L, kind, 5)
+    print(f"case tile blocks {kind} n={n}", flush=True)
+    # one launch clears the energies
+    tr = torch.zeros(n, dtype=torch.int32, device="cuda")
+    launches = hipgraph.kernel_launches(lambda s: rngx.ising_sweep_hits(lat, 0.42, n, hits, tr, stream=s))
+    assert len(launches) <= 1 + n, launches
+    rngx.ising_sweep_hits(lat, 0.42, n, hits, tr)
+    assert np.array_equal(tr.cpu().numpy(), orc.ising_sweeps(L, kind, 0.42, st, sp, n, hits=hits))
+    assert np.array_equal(rngx.ising_get_spins(lat).ravel(), sp)
+    assert np.array_equal(rngx.rng_get_state(rngx.ising_rng(lat)), st)
