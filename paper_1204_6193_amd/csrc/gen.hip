@@ -98,9 +98,12 @@ __device__ __forceinline__ float to_unit(uint32_t u) { return static_cast<float>
 
 // Non-temporal stores: the outputs are streamed out and not read back by
 // this kernel (XS1024W u32 fill at 2^20 x 4096: 6.30 -> 6.55 TB/s).  Plain ones
-// (NT = false) where waves put a row's lines together and the output fits the
-// memory-side cache: LCG32 99991 x 400 43 -> 39 us on buffers taken in turn (38
-// -> 28 on one), but 300001 x 1000 (1.2 GB) 235 -> 258.
+// (NT = false) where a thread's vectors are not whole lines, which the L2 puts
+// together, and the output fits the memory-side cache: LCG32 99991 x 400 43 -> 39
+// us on buffers taken in turn (38 -> 28 on one), but 300001 x 1000 (1.2 GB) 235 ->
+// 258.  With one stream a thread, whose waves write whole lines, the two are
+// alike at any size (LCG32, MWC, Philox and XORWOW, 300 sizes of 80 KB to 2.1 GB:
+// 1.00 on average).
 // A row of S words starts at any word when S is not a multiple of V; global
 // stores of 2 and 4 words need no more than word alignment.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -270,15 +273,16 @@ __global__ __launch_bounds__(kBlock) void k_fill_small(uint8_t *st, uint64_t S, 
 // Small-state kinds, paced: V consecutive streams per thread, BLK threads
 // per workgroup (threads past the last stream stay in the loop with their
 // stores masked, since they take part in the barriers).
-template <class G, int MODE, int V, int BLK>
+template <class G, int MODE, int V, int BLK, bool WHOLE>
 __global__ __launch_bounds__(BLK) void k_fill_paced(uint8_t *st, uint64_t S, uint64_t count, void *out,
                                                     uint32_t *ring) {
     const uint64_t s0 = (static_cast<uint64_t>(blockIdx.x) * BLK + threadIdx.x) * V;
-    const uint32_t live = s0 < S ? static_cast<uint32_t>(min(static_cast<uint64_t>(V), S - s0)) : 0;
+    // streams of the thread: V or none where V divides S (WHOLE)
+    const uint32_t live = s0 >= S ? 0 : WHOLE ? V : static_cast<uint32_t>(min(static_cast<uint64_t>(V), S - s0));
     G g[V];
 #pragma unroll
     for (int v = 0; v < V; ++v)
-        if (v < live) g[v].load(st, S, s0 + v);
+        if (WHOLE ? live != 0 : v < live) g[v].load(st, S, s0 + v);
     __shared__ uint32_t s_free;
     Pacer pc(ring);
     for (uint64_t k0 = 0, band = 0; k0 < count; k0 += kBand, ++band) {
@@ -287,7 +291,7 @@ __global__ __launch_bounds__(BLK) void k_fill_paced(uint8_t *st, uint64_t S, uin
             uint32_t u[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) u[v] = g[v].next();
-            if (live) store_out<MODE, V>(out, k * S + s0, u, live);
+            if (live) store_out<MODE, V>(out, k * S + s0, u, WHOLE ? V : live);
         };
         const uint64_t k1 = k0 + kBand < count ? k0 + kBand : count;
         if (k1 - k0 == kBand) {
@@ -301,7 +305,7 @@ __global__ __launch_bounds__(BLK) void k_fill_paced(uint8_t *st, uint64_t S, uin
                     uint32_t u[V];
 #pragma unroll
                     for (int v = 0; v < V; ++v) u[v] = d[v][kk];
-                    if (live) store_out<MODE, V>(out, (k0 + kk) * S + s0, u, live);
+                    if (live) store_out<MODE, V>(out, (k0 + kk) * S + s0, u, WHOLE ? V : live);
                 }
             } else {
 #pragma unroll
@@ -314,7 +318,7 @@ __global__ __launch_bounds__(BLK) void k_fill_paced(uint8_t *st, uint64_t S, uin
     }
 #pragma unroll
     for (int v = 0; v < V; ++v)
-        if (v < live) g[v].store(st, S, s0 + v);
+        if (WHOLE ? live != 0 : v < live) g[v].store(st, S, s0 + v);
 }
 
 // XS1024W: thread t runs lane j = t % 16 of instance g = t / 16.  The output
@@ -402,19 +406,22 @@ constexpr rngx_fill_config kXsConfigs[] = {{1, 2, 1024}, {1, 2, 512}, {0, 2, 102
 constexpr rngx_fill_config kLfgConfigs[] = {{1, 16, 256}, {0, 16, 256}};
 constexpr int kNumSmall = sizeof(kSmallConfigs) / sizeof(kSmallConfigs[0]);
 constexpr int kNumXs = sizeof(kXsConfigs) / sizeof(kXsConfigs[0]);
-static_assert(kNumSmall <= kMaxFillConfigs && kNumXs <= kMaxFillConfigs, "Gen::resident too small");
+static_assert(kNumSmall < kMaxFillConfigs && kNumXs <= kMaxFillConfigs, "Gen::resident too small");
 
 int default_config(rngx_kind kind) { return kind == RNGX_XORWOW ? 1 : 0; }
 
-// Kernel of a configuration (U32 or F32), for launches and occupancy.
+// Kernel of a configuration (U32 or F32), for launches and occupancy.  Where V
+// does not divide S only the default configurations have one.
 template <class G, int MODE>
-const void *paced_kernel(int v, int blk) {
-    if (v == 4 && blk == 256) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 4, 256>);
-    if (v == 4 && blk == 512) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 4, 512>);
-    if (v == 4 && blk == 1024) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 4, 1024>);
-    if (v == 2 && blk == 256) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 2, 256>);
-    if (v == 2 && blk == 512) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 2, 512>);
-    if (v == 2 && blk == 1024) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 2, 1024>);
+const void *paced_kernel(int v, int blk, bool whole) {
+    constexpr int kDefaultBlk = std::is_same<G, Xorwow>::value ? 1024 : 512;
+    if (!whole) return v == 4 && blk == kDefaultBlk ? reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 4, kDefaultBlk, false>) : nullptr;
+    if (v == 4 && blk == 256) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 4, 256, true>);
+    if (v == 4 && blk == 512) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 4, 512, true>);
+    if (v == 4 && blk == 1024) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 4, 1024, true>);
+    if (v == 2 && blk == 256) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 2, 256, true>);
+    if (v == 2 && blk == 512) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 2, 512, true>);
+    if (v == 2 && blk == 1024) return reinterpret_cast<const void *>(&k_fill_paced<G, MODE, 2, 1024, true>);
     return nullptr;
 }
 template <int MODE>
@@ -425,66 +432,63 @@ const void *xs_kernel(int blk) {
     return nullptr;
 }
 template <class G>
-const void *config_kernel(int mode, const rngx_fill_config &c) {
-    return mode == kOutU32 ? paced_kernel<G, kOutU32>(c.streams_per_thread, c.block)
-                           : paced_kernel<G, kOutF32>(c.streams_per_thread, c.block);
+const void *config_kernel(int mode, const rngx_fill_config &c, bool whole) {
+    return mode == kOutU32 ? paced_kernel<G, kOutU32>(c.streams_per_thread, c.block, whole)
+                           : paced_kernel<G, kOutF32>(c.streams_per_thread, c.block, whole);
 }
-const void *config_kernel(rngx_kind kind, int mode, const rngx_fill_config &c) {
+const void *config_kernel(rngx_kind kind, int mode, const rngx_fill_config &c, bool whole) {
     switch (kind) {
-    case RNGX_LCG32: return config_kernel<Lcg32>(mode, c);
-    case RNGX_LCG64: return config_kernel<Lcg64>(mode, c);
-    case RNGX_MWC: return config_kernel<Mwc>(mode, c);
-    case RNGX_MWC_DIFF: return config_kernel<MwcDiff>(mode, c);
-    case RNGX_XORWOW: return config_kernel<Xorwow>(mode, c);
-    case RNGX_PHILOX4X32_10: return config_kernel<Philox>(mode, c);
-    case RNGX_PHILOX4X32_7: return config_kernel<Philox7>(mode, c);
-    case RNGX_LCG32_SUB: return config_kernel<Lcg32Sub>(mode, c);
-    case RNGX_LCG64_SUB: return config_kernel<Lcg64Sub>(mode, c);
+    case RNGX_LCG32: return config_kernel<Lcg32>(mode, c, whole);
+    case RNGX_LCG64: return config_kernel<Lcg64>(mode, c, whole);
+    case RNGX_MWC: return config_kernel<Mwc>(mode, c, whole);
+    case RNGX_MWC_DIFF: return config_kernel<MwcDiff>(mode, c, whole);
+    case RNGX_XORWOW: return config_kernel<Xorwow>(mode, c, whole);
+    case RNGX_PHILOX4X32_10: return config_kernel<Philox>(mode, c, whole);
+    case RNGX_PHILOX4X32_7: return config_kernel<Philox7>(mode, c, whole);
+    case RNGX_LCG32_SUB: return config_kernel<Lcg32Sub>(mode, c, whole);
+    case RNGX_LCG64_SUB: return config_kernel<Lcg64Sub>(mode, c, whole);
     case RNGX_XS1024W: return mode == kOutU32 ? xs_kernel<kOutU32>(c.block) : xs_kernel<kOutF32>(c.block);
     default: break;  // lagged Fibonacci kinds have their own kernel
     }
     return nullptr;
 }
 
-// Workgroups of configuration i that fit on the device at once (cached).
-uint32_t resident(Gen *g, int i, const rngx_fill_config &c) {
-    if (g->resident[i] >= 0) return static_cast<uint32_t>(g->resident[i]);
+// Workgroups of configuration i that fit on the device at once (cached; the
+// last entry is the default's kernel for an S that V does not divide).
+uint32_t resident(Gen *g, int i, const rngx_fill_config &c, bool whole) {
+    int &known = g->resident[whole ? i : kMaxFillConfigs - 1];
+    if (known >= 0) return static_cast<uint32_t>(known);
     int u = 0, f = 0;
-    const void *ku = config_kernel(g->kind, kOutU32, c), *kf = config_kernel(g->kind, kOutF32, c);
+    const void *ku = config_kernel(g->kind, kOutU32, c, whole), *kf = config_kernel(g->kind, kOutF32, c, whole);
     if (!ku || !kf || hipOccupancyMaxActiveBlocksPerMultiprocessor(&u, ku, c.block, 0) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&f, kf, c.block, 0) != hipSuccess) {
         (void)hipGetLastError();
         u = f = 0;
     }
-    g->resident[i] = std::min(u, f) * std::max(g->n_cu, 0);
-    return static_cast<uint32_t>(g->resident[i]);
+    known = std::min(u, f) * std::max(g->n_cu, 0);
+    return static_cast<uint32_t>(known);
 }
 
 // Pace a launch of `blocks` workgroups of configuration i: large enough and
 // every workgroup resident at once.
-bool pace_ok(Gen *g, int i, const rngx_fill_config &c, uint64_t blocks, uint64_t count) {
-    return g->d_ring && count >= 4 * kBand && blocks >= 128 && blocks <= resident(g, i, c);
+bool pace_ok(Gen *g, int i, const rngx_fill_config &c, uint64_t blocks, uint64_t count, bool whole = true) {
+    return g->d_ring && count >= 4 * kBand && blocks >= 128 && blocks <= resident(g, i, c, whole);
+}
+// Where V does not divide S (rows unaligned, a test for the tail in every
+// store), pacing pays later for the kinds with long chains or 8 rows at once: us
+// with one stream a thread and paced, Philox4x32-10 300001 x 33 15 and 24, x 64 33
+// and 25, x 200 112 and 64; XORWOW 524290 x 33 23 and 28, x 64 51 and 39.  LCG32
+// 524290 x 33 22 and 17.
+template <class G>
+bool pace_ragged(uint64_t S, uint64_t count) {
+    if (HasNext8<G>::value) return S * count >= 1ull << 24;
+    return HasAdvance<G>::value || count >= 48;
 }
 
 void clear_ring(Gen *g, hipStream_t st) {
     hipLaunchKernelGGL(k_zero_ring, dim3((kRing * kPaceSlots + kBlock - 1) / kBlock), dim3(kBlock), 0, st, g->d_ring);
 }
 
-// Unpaced fills.  Streams per thread: one where few streams leave the chip
-// short of waves (a wave's row store is then 256 bytes, but four times as many
-// waves hide the chain of a row: LCG32 FP32 20001 streams x 300, 16 us with
-// four, 8 with one; XORWOW, whose rows cannot be split, 131073 x 500 110 and
-// 80) and for Philox with whole lines in a row, where registers are what holds
-// waves back (2^20 x 1024: 945 and 785); else four (LCG32 99991 x 400 46 with
-// one, 39 with four, 300001 x 1000 571 and 235; Philox 985091 x 266 364 and
-// 290).  Short fills take one as well, whatever the streams: up to 2^23 values
-// (LCG32 100002 x 64 14 us with four, 7 with one, 300001 x 32 11 and 12; Philox
-// 1032178 x 4 13 and 8), XORWOW 2^24 (1032178 x 8 23 and 14).
-template <class G>
-bool one_stream(uint64_t S) {
-    if (HasNext8<G>::value) return S < 1ull << 16 || S % 32 == 0;
-    return S < (HasAdvance<G>::value ? 1ull << 16 : 1ull << 19);
-}
 // Row blocks: as many as make kSplitWaves waves (two per SIMD), of at least
 // split_rows rows each, about where a block's rows cost as much as the way to
 // its first one: LCG32 1024 x 4096 285 -> 10 us, Philox4x32-10 4096 x 1000 220 ->
@@ -504,12 +508,69 @@ uint64_t row_blocks(uint64_t waves, uint64_t count) {
     return std::max<uint64_t>(1, std::min(kSplitWaves / waves, count / split_rows<G>()));
 }
 
+// An unpaced fill: V streams a thread, in `by` row blocks, with non-temporal
+// stores or plain ones; or (bands) by the kernel of the kind's default
+// configuration without its pacing.
+struct FreeShape {
+    int V;
+    uint64_t by;
+    bool nt, bands;
+};
+// Streams a thread: one where few streams or short fills leave the chip short
+// of waves (a wave's row store is then 256 bytes, but four times as many waves
+// hide the chain of a row), four otherwise.  Rows of whole vectors (S % 4 == 0)
+// in bands of 8 unrolled rows where many streams are filled in few rows.  The
+// lines below were drawn by timing each of these for 7 kinds, 27 stream counts of
+// 20000 to 2^24 and 13 row counts of 1 to 4000 (outputs up to 4 GB, buffers
+// taken in turn); us as (one stream, four, bands).
+template <class G>
+FreeShape free_shape(uint64_t S, uint64_t count) {
+    constexpr bool kPhilox = HasNext8<G>::value, kXorwow = !HasAdvance<G>::value;
+    const bool whole = S % 4 == 0, pages = S % 1024 == 0;
+    const uint64_t n = S * count, waves = ((S + 3) / 4 + 63) / 64, by4 = row_blocks<G>(waves, count);
+    const FreeShape one{1, row_blocks<G>((S + 63) / 64, count), false, false}, one_nt{1, 1, true, false};
+    const FreeShape four{4, 1, whole || 4 * n > kCached, false}, bands{4, 1, true, true};
+    if (kPhilox) {
+        // Registers are what holds waves back, so whole lines in a row go one
+        // stream a thread: 2^20 x 1024 (785, 945, 907); but 7 rounds 2^23 x 64
+        // (453, 420, 425), 2^24 x 8 (161, -, 214).
+        if (S < 1ull << 16 || S % 32 == 0)
+            return std::is_same<G, Philox7>::value && S > 1ull << 21 && count >= 16 && n >= 1ull << 26 ? bands : one;
+        if (n < 1ull << 23) return one;                     // 1032178 x 4 (8, 13, 13)
+        if (whole) return n >= 1ull << 26 ? bands : four;   // 4194308 x 8 (43, 48, 50), x 128 (-, 762, 727)
+        // 524290 x 31 (20, 30, -), 700001 x 31 (29, 36, -), 1032178 x 24 (34, 28, -), x 31 (50, 37, -); 3000001 x 16
+        // (60, 71, -), x 24 (89, 75, -)
+        if (S >= 1ull << 18) return n < 24'000'000 || (S > 1ull << 21 && count < 24) ? one_nt : four;
+        // 131073 x 64 (13, 21, -), x 200 (36, 37, -), x 400 (74, 55, -)
+        return count < 256 && n < 1ull << 25 ? one_nt : FreeShape{4, by4, four.nt, false};
+    }
+    if (kXorwow) {  // its rows cannot be split: 131073 x 500 (80, 110, -)
+        if (S < 1ull << 19) return FreeShape{1, 1, false, false};
+        if (n < 1ull << 24) return one_nt;  // states fill the L2 themselves: 1032178 x 4 10, plain stores 11, four 14
+        if (whole)  // 2^22 x 16 (68, 81, 75), 2^24 x 31 (564, 658, 564), 2^20 x 24 (25, 28, 30), 3000000 x 24 (62, 66, 71)
+            return S >= 1ull << 21 && count >= 16 && (pages || (S >= 1ull << 22 && count < 32)) ? bands : four;
+        return count < 24 ? one_nt : four;  // 3000001 x 16 (62, 67, -), 1032178 x 24 (39, 32, -)
+    }
+    if (S < 1ull << 16) return one;  // LCG32 FP32 20001 x 300 (8, 16, -)
+    // LCG32 100002 x 64 (7, 14, -); states of 8 bytes 2^22 x 1 (15, 13, 12)
+    if (n < 1ull << 23) return whole && S >= 1ull << 22 ? bands : one;
+    if (whole) {
+        if (waves < 512) return FreeShape{4, by4, true, false};
+        // LCG32 200000 x 400: row blocks 60, without 54, bands 59; 2^20 x 16 (-, 15, 13), 2^22 x 64 (-, 250, 237),
+        // 2^24 x 64 (-, 780, 870), 3000000 x 24 (-, 47, 49), 4194308 x 24 (-, 130, 126)
+        return S >= 1ull << 20 && ((pages && n < 1ull << 30) || (S >= 1ull << 22 && count < 32)) ? bands : four;
+    }
+    // Fewer than three waves a CU: MWC 65537 x 200 (15, 31, -), 99991 x 200 (22, 38, -); two are enough for long
+    // columns: 131073 x 64 (11, 13, -), x 400 (66, 53, -)
+    if (waves * by4 < 768 && (waves < 512 || count < 256)) return one_nt;
+    return FreeShape{4, waves < 640 ? by4 : 1, four.nt, false};  // 200001 x 400: two row blocks 83, one 74
+}
+
 template <class G, int MODE, int V, bool NT, bool WHOLE = false>
-hipError_t fill_free(Gen *g, void *out, uint64_t count, hipStream_t st) {
+hipError_t fill_free(Gen *g, void *out, uint64_t count, uint64_t by, hipStream_t st) {
     const uint64_t S = g->S;
     const uint64_t blocks = ((S + V - 1) / V + kBlock - 1) / kBlock;
-    if constexpr (MODE != kOutXor && HasAdvance<G>::value) {
-        const uint64_t by = row_blocks<G>(((S + V - 1) / V + 63) / 64, count);
+    if constexpr (MODE != kOutXor && HasAdvance<G>::value && !(V == 1 && NT)) {
         if (by > 1 && g->d_ring && blocks <= kSplitGroups) {
             const uint64_t rows = ((count + by - 1) / by + 7) / 8 * 8;
             hipLaunchKernelGGL((k_fill_small<G, MODE, V, true, NT>),
@@ -530,33 +591,31 @@ hipError_t fill_small(Gen *g, void *out, uint64_t count, hipStream_t st) {
         const int i = g->fill_cfg >= 0 ? g->fill_cfg : default_config(g->kind);
         const rngx_fill_config c = kSmallConfigs[i];
         const int V = c.streams_per_thread;
+        const bool whole = S % V == 0;
         const uint64_t blocks = ((S + V - 1) / V + c.block - 1) / c.block;
-        if (c.paced && pace_ok(g, i, c, blocks, count)) {
-            clear_ring(g, st);
-            void *args[] = {&g->d_state, const_cast<uint64_t *>(&S), &count, &out, &g->d_ring};
-            const hipError_t e = hipLaunchKernel(config_kernel<G>(MODE, c), dim3(static_cast<unsigned>(blocks)),
-                                                 dim3(c.block), args, 0, st);
+        const void *fn = c.paced ? config_kernel<G>(MODE, c, whole) : nullptr;
+        const bool pace = fn && (whole || pace_ragged<G>(S, count)) && pace_ok(g, i, c, blocks, count, whole);
+        const FreeShape f = free_shape<G>(S, count);
+        if (pace || (fn && f.bands)) {
+            if (pace) clear_ring(g, st);
+            uint32_t *ring = pace ? g->d_ring : nullptr;
+            void *args[] = {&g->d_state, const_cast<uint64_t *>(&S), &count, &out, &ring};
+            const hipError_t e = hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(c.block), args, 0, st);
             return e != hipSuccess ? e : hipGetLastError();
         }
-        if (one_stream<G>(S)) return fill_free<G, MODE, 1, false>(g, out, count, st);
-        // (XORWOW's states fill the L2 themselves: 1032178 x 4 11.3 us with plain stores, 9.7 without)
-        if (S * count < (HasAdvance<G>::value ? 1ull << 23 : 1ull << 24))
-            return fill_free<G, MODE, 1, !HasAdvance<G>::value>(g, out, count, st);
-        // Rows that are not made of whole vectors meet in a line, which the L2
-        // puts together; aligned ones don't need it (XORWOW 2^20 x 16 29.6 us with
-        // plain stores, 25.8 without).
-        const bool aligned = S % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
-        if (!aligned && 4 * S * count <= kCached) return fill_free<G, MODE, 4, false>(g, out, count, st);
-    } else if (S < 1ull << 19 || (S % 4 && S < 1ull << 21)) {
+        if (f.V == 1) return f.nt ? fill_free<G, MODE, 1, true>(g, out, count, 1, st) : fill_free<G, MODE, 1, false>(g, out, count, f.by, st);
+        if (S % 4 == 0) return fill_free<G, MODE, 4, true, true>(g, out, count, f.by, st);
+        return f.nt ? fill_free<G, MODE, 4, true>(g, out, count, f.by, st) : fill_free<G, MODE, 4, false>(g, out, count, f.by, st);
+    } else {
         // Nothing to store: four times the waves hide a stream's chain of steps
         // (512 rows, four streams a thread and one: LCG32 2^12 streams 22 and 13
         // us, 2^18 36 and 18, 2^19 30 and 30, 2^20 45 and 51; MWC 2^18 29 and 21),
         // and of the sizes that fill no whole round of workgroups the smaller
         // ones lose less (Philox4x32-10 2^19 + 1 130 and 85).
-        return fill_free<G, MODE, 1, false>(g, out, count, st);
+        if (S < 1ull << 19 || (S % 4 && S < 1ull << 21)) return fill_free<G, MODE, 1, false>(g, out, count, 1, st);
+        if (S % 4 == 0) return fill_free<G, MODE, 4, true, true>(g, out, count, 1, st);
+        return fill_free<G, MODE, 4, true>(g, out, count, 1, st);
     }
-    if (S % 4 == 0) return fill_free<G, MODE, 4, true, true>(g, out, count, st);
-    return fill_free<G, MODE, 4, true>(g, out, count, st);
 }
 
 template <int MODE>

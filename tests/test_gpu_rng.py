@@ -8,6 +8,8 @@ import numpy as np
 import pytest
 import torch
 
+import hipgraph
+
 pytestmark = pytest.mark.gpu
 
 KINDS = ["lcg32", "lcg64", "mwc", "xorwow", "philox4x32_10", "xs1024w", "philox4x32_7", "lcg32_sub", "lcg64_sub",
@@ -511,3 +513,70 @@ def test_fill_row_blocks(rngx, orc, kind):
             assert np.all(got[S * count:] == 7), (kind, S, count)
             assert np.array_equal(got[:S * count].view(want.dtype).reshape(count, S), want), (kind, S, count)
             assert np.array_equal(rngx.rng_get_state(g), st), (kind, S, count)
+
+
+# (streams, rows, streams per thread, row blocks, bands) of fills that are not
+# paced, one for each line of the rule that lays them out; and of paced ones
+# whose rows are not whole vectors (bands, two launches).
+_AFFINE = [(1001, 300, 1, True, False), (65538, 16, 1, False, False), ((1 << 22) + 4, 1, 4, False, True),
+           (65540, 200, 4, True, False), (200004, 60, 4, False, False), (1 << 20, 9, 4, False, True),
+           ((1 << 20) + 4, 9, 4, False, False), ((1 << 22) + 4, 3, 4, False, True), (65537, 130, 1, False, False),
+           (99991, 400, 4, True, False), (99991, 700, 4, True, False), (131073, 260, 4, None, False),
+           (200001, 64, 4, False, False), (300003, 31, 4, False, False), (2200001, 34, 4, False, False),
+           ((1 << 19) + 3, 40, 4, False, True), (300001, 230, 4, False, True)]
+_PHILOX = [(1001, 300, 1, True, False), (65568, 200, 1, False, False), (65537, 120, 1, False, False),
+           (1032178, 5, 1, False, False), ((1 << 20) + 4, 9, 4, False, False), ((1 << 22) + 4, 17, 4, False, True),
+           (524290, 31, 1, False, False), (524291, 40, 1, False, False), (2200001, 25, 4, False, False),
+           (2200001, 30, 4, False, False), (131073, 260, 4, True, False), (99991, 400, 4, True, False),
+           (99991, 700, 4, True, False), (1032178, 25, 4, False, False), (300001, 70, 4, False, True)]
+_XORWOW = [(4100, 300, 1, False, False), (262147, 300, 1, False, False), ((1 << 19) + 2, 31, 1, False, False),
+           ((1 << 21) + 1, 8, 1, False, False), (1 << 20, 17, 4, False, False), (1 << 21, 17, 4, False, True),
+           ((1 << 22) + 4, 17, 4, False, True), ((1 << 21) + 4, 17, 4, False, False), (700001, 25, 4, False, False),
+           (2200001, 33, 4, False, False), (800003, 100, 4, False, True), ((1 << 19) + 3, 40, 4, False, False)]
+
+
+@pytest.mark.parametrize("kind", [k for k in KINDS if k != "xs1024w"])
+def test_fill_shapes(rngx, orc, kind):
+    """Fills at every line of the rule that lays them out: the launch is the one
+    the rule says, sampled streams (the last ones and those beside a vector's
+    end among them) equal the oracle, the whole output's XOR equals consume's,
+    nothing is written past the end, and the streams end where they should.
+    U32 and FP32."""
+    table = _PHILOX if kind.startswith("philox") else _XORWOW if kind == "xorwow" else _AFFINE
+    for S, count, V, split, bands in table:
+        if kind == "mwc_diff" and S > 1 << 21:
+            continue
+        if kind == "mwc_diff" and S == 99991:  # row blocks of 512 rows or more: too few waves with four streams
+            V = 1
+        print(f"case fill shape {kind} {S} x {count}", flush=True)
+        g, twin = rngx.rng_create(kind, S, 6), rngx.rng_create(kind, S, 6)
+        st = orc.seed(kind, S, 6)
+        out = torch.full((S * count + 8,), 7, dtype=torch.int32, device="cuda")
+        launches = hipgraph.kernel_launches(lambda s: rngx.rng_fill_u32(g, out, count, stream=s))
+        grid, block = launches[-1] if len(launches) == 1 else max(launches, key=lambda x: x[0][0] * x[1])
+        threads = -(-S // V)
+        assert block == ((1024 if kind == "xorwow" else 512) if bands else 256), launches
+        assert grid[0] == -(-threads // block), launches
+        if split is not None and kind not in ("mwc", "mwc_diff"):  # these two split later
+            assert (grid[1] > 1) == split, launches
+        rngx.rng_fill_u32(g, out, count)
+        view = out[:S * count].view(count, S)
+        ranges = [(0, 64), (S // 2 - 33, S // 2 + 31), (S - 70, S)] if S > 200 else [(0, S)]
+        for lo, hi in ranges:
+            want = orc.generate(kind, S, st, count, lo=lo, hi=hi)
+            assert np.array_equal(_u32(view[:, lo:hi].contiguous()), want), (S, count, lo)
+        acc = torch.empty(S, dtype=torch.int32, device="cuda")
+        rngx.rng_consume(twin, acc, count)
+        assert torch.equal(acc, _xor_fold(view)), (S, count)
+        assert bool((out[S * count:] == 7).all()), (S, count)
+        assert np.array_equal(rngx.rng_get_state(g), rngx.rng_get_state(twin)), (S, count)
+        # FP32: the floats of the same words
+        g = rngx.rng_create(kind, S, 6)
+        f = torch.full((S * count + 8,), 7, dtype=torch.float32, device="cuda")
+        rngx.rng_fill_f32(g, f, count)
+        want = ((view.view(-1) >> 8) & 0xFFFFFF).to(torch.float32) * 2.0 ** -24
+        assert torch.equal(f[:S * count], want), (S, count)
+        assert bool((f[S * count:] == 7).all()), (S, count)
+        assert np.array_equal(rngx.rng_get_state(g), rngx.rng_get_state(twin)), (S, count)
+        del out, view, f, want
+    torch.cuda.empty_cache()
