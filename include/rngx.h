@@ -213,7 +213,11 @@ rngx_status rng_skip(rngx_gen g, uint64_t n, void *stream);
  * sizes or devices may prefer others).  Pacing keeps the workgroups of a
  * large fill within a few bands of rows of each other, which HBM rewards for
  * the interleaved layout; it needs every workgroup resident and is skipped
- * otherwise.  rng_consume and rng_fill_ragged_u32 do not use these.
+ * otherwise.  An entry chosen by index is then run without it; with the kind's
+ * default (-1), and where the streams per thread do not divide S, the library
+ * picks the streams per thread of an unpaced fill by its size and may cut the
+ * rows of few streams into blocks.  rng_consume and rng_fill_ragged_u32 do not
+ * use these.
  *
  * rng_fill_configs: the list for `kind` in index order; out (n entries) may
  * be NULL to ask for *n only.
@@ -221,7 +225,7 @@ rngx_status rng_skip(rngx_gen g, uint64_t n, void *stream);
  * default); rng_get_fill_config: the entry in use (the default resolved).
  * rng_autotune_fill: times every entry on this handle's fills of `count`
  * outputs per stream into d_out (S*count u32 elements, overwritten), one
- * warm-up and `reps` (>= 1) timed launches each, selects the fastest and
+ * warm-up and `reps` (>= 1) timed launches each (the default entry as -1), selects the fastest and
  * leaves the stream state as it was (it is saved to device memory that the
  * call allocates and frees).  ms_out (may be NULL) receives the mean launch
  * time of each entry in index order.  Synchronizes the stream. */

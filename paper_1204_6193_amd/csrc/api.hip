@@ -411,7 +411,8 @@ rngx_status rng_autotune_fill(rngx_gen h, uint32_t *d_out, uint64_t count, int32
     int best = -1;
     float best_ms = 0;
     for (int i = 0; i < k && e == hipSuccess; ++i) {
-        g->fill_cfg = i;
+        // the default entry stands for the default, whose unpaced fills are laid out by their size
+        g->fill_cfg = i == fill_default(g->kind) ? -1 : i;
         e = hipMemcpyAsync(g->d_state, saved, g->state_bytes, hipMemcpyDeviceToDevice, st);
         if (e == hipSuccess) e = launch_fill(g, d_out, count, kOutU32, st);  // warm-up
         if (e == hipSuccess) e = hipEventRecord(e0, st);
@@ -430,7 +431,7 @@ rngx_status rng_autotune_fill(rngx_gen h, uint32_t *d_out, uint64_t count, int32
     // the stream state as it was before the call
     if (e == hipSuccess) e = hipMemcpyAsync(g->d_state, saved, g->state_bytes, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    g->fill_cfg = best;
+    g->fill_cfg = best == fill_default(g->kind) ? -1 : best;
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     (void)hipFree(saved);

@@ -588,15 +588,17 @@ template <class G, int MODE>
 hipError_t fill_small(Gen *g, void *out, uint64_t count, hipStream_t st) {
     const uint64_t S = g->S;
     if constexpr (MODE != kOutXor) {
-        const int i = g->fill_cfg >= 0 ? g->fill_cfg : default_config(g->kind);
+        const bool set = g->fill_cfg >= 0;
+        const int i = set ? g->fill_cfg : default_config(g->kind);
         const rngx_fill_config c = kSmallConfigs[i];
         const int V = c.streams_per_thread;
         const bool whole = S % V == 0;
         const uint64_t blocks = ((S + V - 1) / V + c.block - 1) / c.block;
         const void *fn = c.paced ? config_kernel<G>(MODE, c, whole) : nullptr;
         const bool pace = fn && (whole || pace_ragged<G>(S, count)) && pace_ok(g, i, c, blocks, count, whole);
-        const FreeShape f = free_shape<G>(S, count);
-        if (pace || (fn && f.bands)) {
+        // a configuration the caller chose is run as it is, paced or not, where its vectors divide a row
+        const FreeShape f = set && whole ? FreeShape{4, 1, true, c.paced != 0} : free_shape<G>(S, count);
+        if (pace || f.bands) {
             if (pace) clear_ring(g, st);
             uint32_t *ring = pace ? g->d_ring : nullptr;
             void *args[] = {&g->d_state, const_cast<uint64_t *>(&S), &count, &out, &ring};

@@ -580,3 +580,36 @@ def test_fill_shapes(rngx, orc, kind):
         assert np.array_equal(rngx.rng_get_state(g), rngx.rng_get_state(twin)), (S, count)
         del out, view, f, want
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("kind", ["lcg32", "mwc", "philox4x32_10", "xorwow"])
+def test_chosen_configuration_is_run(rngx, orc, kind):
+    """A configuration set by index is the one that runs, also where the fill
+    is too small to be paced: its block, its streams per thread, no row blocks.
+    Where those do not divide S the fill is laid out by its size, as with the
+    default."""
+    for S, count in ((1000, 300), (4096, 20), (1 << 18, 9)):
+        for index, (paced, V, block) in enumerate(rngx.rng_fill_configs(kind)):
+            print(f"case chosen configuration {kind} #{index} {S} x {count}", flush=True)
+            g = rngx.rng_create(kind, S, 3)
+            rngx.rng_set_fill_config(g, index)
+            out = torch.empty(S * count, dtype=torch.int32, device="cuda")
+            launches = hipgraph.kernel_launches(lambda s: rngx.rng_fill_u32(g, out, count, stream=s))
+            assert launches == [((-(-S // V // block), 1), block)], (paced, V, block)
+            rngx.rng_fill_u32(g, out, count)
+            st = orc.seed(kind, S, 3)
+            assert np.array_equal(_u32(out).reshape(count, S), orc.generate(kind, S, st, count))
+            assert np.array_equal(rngx.rng_get_state(g), st)
+            rngx.rng_set_fill_config(g, -1)
+            default = hipgraph.kernel_launches(lambda s: rngx.rng_fill_u32(g, out, count, stream=s))
+            h = rngx.rng_create(kind, S, 3)
+            assert default == hipgraph.kernel_launches(lambda s: rngx.rng_fill_u32(h, out, count, stream=s))
+    # few streams: the default cuts the rows of the kinds that jump cheaply, and the tuner may keep it
+    g = rngx.rng_create(kind, 1024, 3)
+    out = torch.empty(1024 * 4096, dtype=torch.int32, device="cuda")
+    default = hipgraph.kernel_launches(lambda s: rngx.rng_fill_u32(g, out, 4096, stream=s))
+    assert (default[0][0][1] > 1) == (kind != "xorwow")
+    ms = rngx.rng_autotune_fill(g, out, 4096, reps=2)
+    tuned = hipgraph.kernel_launches(lambda s: rngx.rng_fill_u32(g, out, 4096, stream=s))
+    if int(np.argmin(ms)) == rngx.rng_get_fill_config(rngx.rng_create(kind, 1024, 3)):
+        assert tuned == default
