@@ -1061,10 +1061,10 @@ hipError_t run_passes(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
 template <class Unit, bool MH>
 hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t *tr, hipStream_t st, uint32_t hits) {
     const IsingPlan &pl = lat->plan;
-    const void *fn = pl.bits ? bits_kernel_for(lat->gen->kind, pl.bits_slots, MH, pl.nwg > 1)
-                             : strip_kernel_for<Unit, MH>(pl.spt, pl.early);
-    const dim3 block(pl.bits ? pl.bits_threads : pl.threads);
-    const uint32_t lds = pl.bits ? bits_lds_bytes(lat->gen->kind, pl.bits_threads, pl.bits_slots) : pl.lds;
+    const BitsShape &bs = MH ? pl.multi : pl.one;
+    const void *fn = pl.bits ? bits_kernel_for(lat->gen->kind, bs.slots, MH, pl.nwg > 1) : strip_kernel_for<Unit, MH>(pl.spt, pl.early);
+    const dim3 block(pl.bits ? bs.threads : pl.threads);
+    const uint32_t lds = pl.bits ? bits_lds_bytes(lat->gen->kind, bs.threads, bs.slots) : pl.lds;
     if (MH && !pl.bits) {
         // The plan was sized with the single-hit kernel: give this one the
         // same LDS and check that every strip can still be resident.
@@ -1083,7 +1083,7 @@ hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
         lat->epoch = 0;
     }
     StripArgs a{lat->d_spins, lat->gen->d_state, lat->gen->S, lat->L, pl.R, pl.nwg, pl.units, T4, T8, n,
-                tr, lat->d_halo, static_cast<uint32_t>(lat->epoch), lat->d_err, hits, pl.R, 0, 0, pl.VB};
+                tr, lat->d_halo, static_cast<uint32_t>(lat->epoch), lat->d_err, hits, pl.R, 0, 0, bs.VB};
     void *args[] = {&a};
     hipError_t e;
     if (pl.nwg == 1)
@@ -1102,12 +1102,17 @@ hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
 // divide R (its far rows are its own), strips of a lattice nt / (32 / NB)
 // tagged words in the L / 2 of their halo slot.  Of the shapes that fit, the
 // one with the fewest instructions on a SIMD per pass is taken: more threads
-// take fewer slots each, but every wave pays for the pass itself.  False where
+// take fewer slots each, but every wave pays for the pass itself.  A multi-hit
+// pass (hits) is mostly draws, in chains that one or two waves of a SIMD cannot
+// hide, so it counts for two and a half at least: Philox 4x32-10 L = 128, 8 sweeps
+// of 10 hits, 256 threads of 16 slots 222 us, 1024 of 4 152; LCG64 L = 1040, 320
+// of 6 slots 109, 832 of 2 94; LCG32 L = 64, 256 of 4 slots 36, 512 of 2 33, 1024
+// of 1 39.  False where
 // none fits: the row is then too ragged for XS1024W (L / 8 threads and VB rows
 // do not meet in 16s within the workgroup) or takes more than 32 sites of a
 // colour per thread, and the strip keeps its spins as bytes.
 bool bits_shape(rngx_kind kind, uint32_t L, uint32_t R, uint32_t nwg, uint32_t NB, uint32_t max_threads,
-                uint32_t max_slots, const std::vector<uint32_t> &slot_list, uint32_t *VB_out, uint32_t *slots_out,
+                uint32_t max_slots, const std::vector<uint32_t> &slot_list, bool hits, uint32_t *VB_out, uint32_t *slots_out,
                 uint32_t *cost_out = nullptr) {
     const uint32_t upr = L / NB;
     uint32_t best = 0xFFFFFFFFu;
@@ -1121,7 +1126,9 @@ bool bits_shape(rngx_kind kind, uint32_t L, uint32_t R, uint32_t nwg, uint32_t N
         for (uint32_t s : slot_list)
             if (s >= H && s <= max_slots) { slots = s; break; }
         if (!slots) continue;
-        const uint32_t cost = (nt + 255) / 256 * (slots * bits_slot_cost(kind) + kBitsPassCost);
+        const uint32_t waves = (nt + 255) / 256;  // on the SIMD with the most
+        const uint32_t cost = hits ? std::max(2 * waves, 5u) * (4 * slots * bits_slot_cost(kind) + 2 * kBitsPassCost)
+                                   : waves * (slots * bits_slot_cost(kind) + kBitsPassCost);
         if (cost <= best) {
             best = cost;
             *VB_out = VB;
@@ -1133,17 +1140,22 @@ bool bits_shape(rngx_kind kind, uint32_t L, uint32_t R, uint32_t nwg, uint32_t N
 }
 
 // Whether the plan's strips can keep their spins as bits (both kernels with
-// every strip resident); fills the plan's shape.
+// every strip resident); fills the plan's shapes.
 bool try_bits(uint32_t L, rngx_kind kind, uint32_t NB, int n_cu, IsingPlan *p) {
     static const std::vector<uint32_t> kSlots = {1, 2, 4, 6, 8, 12, 16};
-    if (!bits_shape(kind, L, p->R, p->nwg, NB, kMaxThreads, 64 / NB, kSlots, &p->VB, &p->bits_slots)) return false;
-    p->bits_threads = (p->VB * (L / NB) + 63) / 64 * 64;
-    for (bool hits : {false, true}) {
-        const void *fn = bits_kernel_for(kind, p->bits_slots, hits, p->nwg > 1);
-        const uint32_t lds = bits_lds_bytes(kind, p->bits_threads, p->bits_slots);
-        if (static_cast<uint64_t>(blocks_per_cu(fn, p->bits_threads, lds)) * n_cu < p->nwg) return false;
-    }
-    return true;
+    auto shape = [&](bool hits, BitsShape *b) {
+        if (!bits_shape(kind, L, p->R, p->nwg, NB, kMaxThreads, 64 / NB, kSlots, hits, &b->VB, &b->slots)) return false;
+        b->threads = (b->VB * (L / NB) + 63) / 64 * 64;
+        return true;
+    };
+    auto resident = [&](bool hits, const BitsShape &b) {
+        const void *fn = bits_kernel_for(kind, b.slots, hits, p->nwg > 1);
+        return static_cast<uint64_t>(blocks_per_cu(fn, b.threads, bits_lds_bytes(kind, b.threads, b.slots))) * n_cu >= p->nwg;
+    };
+    if (!shape(false, &p->one) || !resident(false, p->one)) return false;
+    if (shape(true, &p->multi) && resident(true, p->multi)) return true;
+    p->multi = p->one;  // fewer threads, where several strips share a CU
+    return resident(true, p->multi);
 }
 
 // Try one decomposition into nwg strips; fills *out if it fits on chip.
@@ -1180,7 +1192,7 @@ bool try_strips(uint32_t L, uint32_t nwg, int max_spt, int n_cu, IsingPlan *out)
         if (occ < 1) return false;
         if (static_cast<uint64_t>(occ) * n_cu >= nwg) {
             *out = IsingPlan{true, R, nwg, units, static_cast<uint32_t>(spt), threads, static_cast<uint32_t>(b), early,
-                             false, 0, 0, 0};
+                             false, {}, {}};
             out->bits = try_bits(L, KindOf<Unit>::kind, NB, n_cu, out);
             return true;
         }
@@ -1308,7 +1320,7 @@ bool tile_bits(rngx_kind kind, const BatchShape &sh, uint32_t nb, uint64_t max_u
     for (ReplicaDesc &d : *reps) {
         uint32_t cost = 0;
         const bool on_chip = tile_replica(d.L, nb, max_units, &d, [&](ReplicaDesc *x) {
-            return bits_shape(kind, x->L, x->R, x->nwg, nb, sh.threads, most, slots, &x->VB, &x->slots, &cost);
+            return bits_shape(kind, x->L, x->R, x->nwg, nb, sh.threads, most, slots, false, &x->VB, &x->slots, &cost);
         });
         if (!on_chip) {
             ReplicaDesc y = d;

@@ -614,7 +614,10 @@ __device__ __forceinline__ void bits_strip(const StripArgs &a, uint32_t r, uint3
             return;
         }
     }
-    if constexpr (std::is_same<Unit, SmallUnit<Xorwow>>::value) bits_body<XorwowStripUnit, SPT, MH, GANG>(a, r, lds);
+    // XORWOW multi-hit draws wait on the Weyl word's LDS read each time (L = 1024, 8 sweeps of 10 hits 103 us); up to 8
+    // units of a thread keep it in a register (88)
+    if constexpr (std::is_same<Unit, SmallUnit<Xorwow>>::value && MH && SPT <= 8) bits_body<Unit, SPT, MH, GANG>(a, r, lds);
+    else if constexpr (std::is_same<Unit, SmallUnit<Xorwow>>::value) bits_body<XorwowStripUnit, SPT, MH, GANG>(a, r, lds);
     else if constexpr (std::is_same<Unit, SmallUnit<Lcg32Sub>>::value) bits_body<LcgSubStripUnit<uint32_t>, SPT, MH, GANG>(a, r, lds);
     else if constexpr (std::is_same<Unit, SmallUnit<Lcg64Sub>>::value) bits_body<LcgSubStripUnit<uint64_t>, SPT, MH, GANG>(a, r, lds);
     else bits_body<Unit, SPT, MH, GANG>(a, r, lds);

@@ -65,6 +65,13 @@ struct Ragged {
     std::vector<uint64_t> offsets;   // the request list, kept to re-plan under another shape
 };
 
+// How a strip whose spins are bits lies on its workgroup.
+struct BitsShape {
+    uint32_t VB;       // rows side by side in a workgroup
+    uint32_t slots;    // slots per thread of the kernel
+    uint32_t threads;  // threads per workgroup
+};
+
 // How a lattice is swept: as strips held on chip by co-resident
 // workgroups (strips = true) or by one launch per colour pass.
 struct IsingPlan {
@@ -76,11 +83,8 @@ struct IsingPlan {
     uint32_t threads;  // threads per workgroup
     uint32_t lds;      // dynamic LDS bytes per workgroup
     bool early;        // top and bottom rows in the first and last unit slots
-    // spins as bits (bits = true: the sweeps run k_ising_bits, else k_ising_strip)
-    bool bits;
-    uint32_t VB;            // rows side by side in a workgroup
-    uint32_t bits_slots;    // slots per thread of the kernel
-    uint32_t bits_threads;  // threads per workgroup
+    bool bits;         // spins as bits: the sweeps run k_ising_bits, else k_ising_strip
+    BitsShape one, multi;  // for single-hit and for multi-hit sweeps
 };
 
 // Halo of a lattice cut into nwg strips: two slots of at most L / 2 64-bit

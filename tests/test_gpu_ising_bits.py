@@ -159,3 +159,22 @@ def test_batch_replicas_without_sweeps(rngx, orc, kind):
                 assert int(traces[i][0]) == 7, (shape, i)
             assert np.array_equal(rngx.ising_get_spins(lats[i]).ravel(), sp), (shape, i, Ls[i])
             assert np.array_equal(rngx.rng_get_state(rngx.ising_rng(lats[i])), st), (shape, i, Ls[i])
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("L", [48, 112, 128, 160, 640, 720, 1040])
+def test_multi_hit_shapes(rngx, orc, kind, L):
+    """Multi-hit sweeps lie on more threads than single-hit ones: sides where
+    the two shapes differ, called in turn on one lattice, whose strips exchange
+    rows under both."""
+    lat = rngx.ising_create(L, kind, 3)
+    sp, st = orc.ising_create(L, kind, 3)
+    for n, hits in ((2, 5), (1, 1), (1, 2), (2, 1), (1, 9)):
+        print(f"case bits shapes {kind} L={L} hits={hits} sweeps={n}", flush=True)
+        tr = torch.zeros(n, dtype=torch.int32, device="cuda")
+        rngx.ising_sweep_hits(lat, 0.43, n, hits, tr)
+        want = orc.ising_sweeps(L, kind, 0.43, st, sp, n, hits=hits)
+        assert rngx.ising_status(lat) == 0
+        assert np.array_equal(tr.cpu().numpy(), want)
+        assert np.array_equal(rngx.ising_get_spins(lat).ravel(), sp)
+        assert np.array_equal(rngx.rng_get_state(rngx.ising_rng(lat)), st)
