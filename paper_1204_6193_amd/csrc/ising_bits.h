@@ -110,7 +110,7 @@ __host__ __device__ constexpr uint32_t bits_halo_words(uint32_t nt) { return (nt
 template <class Unit> struct IsPhiloxKey : std::false_type {};
 template <int ROUNDS> struct IsPhiloxKey<PhiloxKeyUnitR<ROUNDS>> : std::true_type {};
 
-// All sweeps of strip r (R rows at row r R0) by the calling workgroup.
+// All sweeps (one at least) of strip r (R rows at row r R0) by the calling workgroup.
 // GANG: several strips (else the strip is the lattice).  TILE: a tile of a
 // lattice in memory (k_ising_tiles), which wraps on itself instead of asking
 // its neighbours and keeps only what lies farther from its edges than the
@@ -596,10 +596,6 @@ __device__ __forceinline__ void bits_body(const StripArgs &a, uint32_t r, uint32
 // all alike, take what they share from the call's start.
 template <class Unit, int SPT, bool MH, bool GANG>
 __device__ __forceinline__ void bits_strip(const StripArgs &a, uint32_t r, uint32_t *lds) {
-    // A batch's replica may have no sweeps: nothing moves.  (Its body makes the
-    // first pass's draws before it enters the loop over the sweeps; testing there
-    // took 2% of a lone strip's pass.)
-    if (a.n_sweeps == 0) return;
     StripArgs b = a;
     if constexpr (std::is_same<Unit, PhiloxUnit>::value || std::is_same<Unit, PhiloxUnit7>::value) {
         using Key = PhiloxKeyUnitR<std::is_same<Unit, PhiloxUnit>::value ? 10 : 7>;
@@ -766,6 +762,9 @@ __global__ __launch_bounds__(MAXT) void k_ising_batch_bits(const ReplicaDesc *re
         if (idx >= n_items) break;  // every workgroup leaves once the list is drained
         const uint2 item = items[idx];
         const ReplicaDesc d = reps[item.x];
+        // No sweeps: nothing moves.  (A strip makes its first pass's draws before it enters the loop over the sweeps;
+        // a test there, or where the strip's form is chosen, cost lone lattices 2%, XORWOW batches up to 18%.)
+        if (d.n_sweeps == 0) continue;
         if (d.mode == kReplicaMemory) {
             replica_in_memory<Unit>(d, red_s);
             continue;
