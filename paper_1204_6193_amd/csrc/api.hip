@@ -705,6 +705,13 @@ static void alloc_tiles(Ising *lat) {
     free_tiles(lat);
 }
 
+// Energy partials of the per-pass path: multi-hit sweeps may take it under a
+// strip plan too (lagged Fibonacci ones always, others with spins as bytes where
+// the multi-hit kernel's strips are not all resident).
+static bool needs_partials(const Ising *lat, const IsingPlan &p) {
+    return !p.strips || !p.bits || is_lfg(lat->gen->kind);
+}
+
 rngx_status ising_create(uint32_t L, rngx_kind kind, uint64_t seed, rngx_ising *out) {
     if (!out) return fail(RNGX_E_INVALID, "out is NULL");
     if (!kind_valid(kind)) return fail(RNGX_E_INVALID, "invalid generator kind " + std::to_string(kind));
@@ -730,8 +737,7 @@ rngx_status ising_create(uint32_t L, rngx_kind kind, uint64_t seed, rngx_ising *
         e = hipMalloc(&lat->d_halo, halo_bytes(lat->plan.nwg, L));
         lat->halo_nwg = lat->plan.nwg;
     }
-    // partials of the per-pass path (lagged Fibonacci multi-hit sweeps take it under any plan)
-    if (e == hipSuccess && (!lat->plan.strips || is_lfg(kind))) e = hipMalloc(&lat->d_partial, 4 * ising_partials(L));
+    if (e == hipSuccess && needs_partials(lat, lat->plan)) e = hipMalloc(&lat->d_partial, 4 * ising_partials(L));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_ising(lat);
@@ -797,7 +803,7 @@ hipError_t apply_plan(Ising *lat, const IsingPlan &p) {
         e = hipMalloc(&lat->d_halo, halo_bytes(p.nwg, L));
         if (e == hipSuccess) lat->halo_nwg = p.nwg;
     }
-    if (e == hipSuccess && (!p.strips || is_lfg(lat->gen->kind)) && !lat->d_partial)
+    if (e == hipSuccess && needs_partials(lat, p) && !lat->d_partial)
         e = hipMalloc(&lat->d_partial, 4 * ising_partials(lat->L));
     if (e == hipSuccess && lat->d_halo)
         e = launch_zero(reinterpret_cast<uint32_t *>(lat->d_halo), halo_bytes(lat->halo_nwg, L) / 4, nullptr);
