@@ -134,6 +134,7 @@ typedef struct {
     uint32_t slots;          /* HIP streams the requests are spread over (>= 1)                 */
     uint32_t max_inflight;   /* requests on the device at once (>= 1); 1 with 1 slot = plain FIFO */
     uint64_t memory_budget;  /* bytes of device memory: request outputs, Ising jobs, jump tables  */
+                             /* (fixed tables of 16 KiB in all come on top)                     */
     uint64_t seed;           /* master seed of every client generator and Ising job              */
 } rngx_server_config;
 

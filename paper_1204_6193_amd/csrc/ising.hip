@@ -14,8 +14,9 @@
 // (ising_bits.h) where a strip's rows divide over its threads so (bits_shape),
 // else, and for the lagged Fibonacci kinds, bytes in LDS (k_ising_strip).
 //
-// Per-pass kernels (larger L): one launch per colour pass, state and spins
-// streamed from memory, energy reduced per block and then across blocks.
+// Larger L: two sweeps or more in tiles (k_ising_tiles), else one launch per
+// colour pass, state and spins streamed from memory, energy reduced per block
+// and then across blocks.
 //
 // Site update: with spins stored as int8 +1 = 0x01, -1 = 0xFF, bit 1 marks a
 // down spin; the number m of neighbours that differ from a site is summed

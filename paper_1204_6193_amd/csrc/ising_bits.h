@@ -660,9 +660,9 @@ const void *bits_kernel_of(int slots, bool hits, bool gang) {
 // state and spin twice per sweep and is bound by that; a block moves them once
 // per n_sweeps and the margins once more, and its loads, all in flight at
 // once, overlap the passes of the CU's other workgroups.  L = 8192, us per
-// sweep of 8, per pass -> tiles: MWC 153 -> 35 (bytes 25, instructions 18),
-// LCG32 126 -> 29, XORWOW 366 -> 89, Philox 4x32-10 226 -> 65, XS1024W
-// 131 -> 68 (its margin of whole instances, 128 columns, costs 1.8 times the
+// sweep of 8, per pass -> tiles: MWC 146 -> 31 (bytes 25, instructions 18),
+// LCG32 123 -> 27, XORWOW 361 -> 87, Philox 4x32-10 226 -> 62, XS1024W
+// 129 -> 78 (its margin of whole instances, 128 columns, costs 1.8 times the
 // instructions).
 // Tiles in the order of the lattice within each of the 8 dies.
 __device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t n) {
@@ -739,8 +739,9 @@ const void *tiles_kernel_of(bool hits) {
 // memory): persistent workgroups take (replica, strip) items as k_ising_batch
 // does.  The slots of a replica are one of three per kind, so that the kernel
 // holds few copies of the strip's body.  60 replicas of L = 16 .. 1024, 50
-// sweeps: XS1024W 1.34 -> 0.72 ms, LCG32 1.32 -> 0.48; 512 such, XS1024W,
-// 1169 -> 1938 updates/ns; 2048 of L <= 128 in 256-thread workgroups 990 -> 1608.
+// sweeps: XS1024W 1.34 -> 0.71 ms, LCG32 1.32 -> 0.48; 512 such, XS1024W,
+// 1169 -> 2054 updates/ns; 2048 of L <= 128 990 (256-thread workgroups) -> 1767
+// (512).
 template <class Unit, int SPT>
 __device__ __forceinline__ void bits_item(const StripArgs &a, uint32_t r, bool gang, uint32_t *lds) {
     if (gang) bits_strip<Unit, SPT, false, true>(a, r, lds);

@@ -73,7 +73,7 @@ struct BitsShape {
 };
 
 // How a lattice is swept: as strips held on chip by co-resident
-// workgroups (strips = true) or by one launch per colour pass.
+// workgroups (strips = true) or from memory, in tiles or per colour pass.
 struct IsingPlan {
     bool strips;
     uint32_t R;        // rows per strip
@@ -101,7 +101,7 @@ struct Ising {
     uint64_t *d_halo;    // strips: halo_bytes of tagged words (spins | pass tag << 32)
     uint32_t halo_nwg;   // strips the halo allocation is sized for
     uint32_t *d_err;     // strips: set if a neighbour wait gave up
-    int32_t *d_partial;  // per-pass path: per-block energy partials
+    int32_t *d_partial;  // per-pass path: per-block energy partials (null where no sweep takes it)
     int8_t *alt_spins;   // tiled sweeps: the images every second block writes (null where sweeps run per pass)
     uint8_t *alt_state;
     uint64_t epoch;      // passes run since the halo tags were last cleared
