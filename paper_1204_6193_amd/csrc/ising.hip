@@ -1077,11 +1077,21 @@ hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
         hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<unsigned>((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
                            reinterpret_cast<uint32_t *>(tr), n);
     }
-    if (pl.nwg > 1 && lat->epoch + 2 * n + 3 >= (1ull << 31)) {  // restart the pass tags before they wrap
-        const uint64_t words = halo_bytes(pl.nwg, lat->L) / 4;
-        hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<unsigned>((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
-                           reinterpret_cast<uint32_t *>(lat->d_halo), words);
-        lat->epoch = 0;
+    if (pl.nwg > 1) {
+        // Clear the halo where its tags would repeat: before they wrap, and in
+        // every replay of a captured call, whose tags are those of the replay before.
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess) {  // the default stream beside another one's capture: the launch decides
+            (void)hipGetLastError();
+            cap = hipStreamCaptureStatusNone;
+        }
+        const bool captured = cap != hipStreamCaptureStatusNone, wrap = !captured && lat->epoch + 2 * n + 3 >= (1ull << 31);
+        if (captured || wrap) {
+            const uint64_t words = halo_bytes(pl.nwg, lat->L) / 4;
+            hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<unsigned>((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
+                               reinterpret_cast<uint32_t *>(lat->d_halo), words);
+        }
+        if (wrap) lat->epoch = 0;
     }
     StripArgs a{lat->d_spins, lat->gen->d_state, lat->gen->S, lat->L, pl.R, pl.nwg, pl.units, T4, T8, n,
                 tr, lat->d_halo, static_cast<uint32_t>(lat->epoch), lat->d_err, hits, pl.R, 0, 0, bs.VB};

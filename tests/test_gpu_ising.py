@@ -615,3 +615,36 @@ def test_philox_strips_with_uneven_positions(rngx, orc, kind):
         assert np.array_equal(tr.cpu().numpy(), want), rep
         assert np.array_equal(rngx.ising_get_spins(lat).ravel(), sp), rep
         assert np.array_equal(rngx.rng_get_state(g), st), rep
+
+
+@pytest.mark.parametrize("kind", ["lcg32", "xs1024w", "philox4x32_10", "lfg521"])
+@pytest.mark.parametrize("n,hits", [(1, 1), (2, 1), (1, 3)])
+def test_strips_in_a_graph(rngx, orc, kind, n, hits):
+    """A graph of sweeps in strips, replayed with eager calls between: no replay
+    takes the boundary rows of the one before for its own."""
+    L = 512
+    lat = rngx.ising_create(L, kind, 6)
+    assert rngx.ising_info(lat)["strips"] > 1
+    sp, st = orc.ising_create(L, kind, 6)
+    tr = torch.zeros(n, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        rngx.ising_sweep_hits(lat, 0.42, n, hits, tr)
+
+    def check(sweeps, k, got):
+        want = orc.ising_sweeps(L, kind, 0.42, st, sp, sweeps, **({} if k == 1 else {"hits": k}))
+        assert rngx.ising_status(lat) == 0
+        assert np.array_equal(got.cpu().numpy(), want)
+        assert np.array_equal(rngx.ising_get_spins(lat).ravel(), sp)
+        assert np.array_equal(rngx.rng_get_state(rngx.ising_rng(lat)), st)
+
+    te = torch.zeros(2, dtype=torch.int32, device="cuda")
+    for replay in range(4):
+        print(f"case strips graph {kind} n={n} hits={hits} replay={replay}", flush=True)
+        g.replay()
+        torch.cuda.synchronize()
+        check(n, hits, tr)
+        if replay == 1:
+            rngx.ising_sweep(lat, 0.42, 2, te)
+            check(2, 1, te)
