@@ -1077,15 +1077,20 @@ hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
         hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<unsigned>((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
                            reinterpret_cast<uint32_t *>(tr), n);
     }
+    bool captured = false;
     if (pl.nwg > 1) {
         // Clear the halo where its tags would repeat: before they wrap, and in
-        // every replay of a captured call, whose tags are those of the replay before.
+        // every replay of a captured call, whose tags are those of the replay
+        // before.  Captured calls take tags from 2^31 on, other calls the ones
+        // below: whatever a replay leaves in the halo, under any later plan
+        // and after any wrap, is no tag that another call waits for.
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) != hipSuccess) {  // the default stream beside another one's capture: the launch decides
             (void)hipGetLastError();
             cap = hipStreamCaptureStatusNone;
         }
-        const bool captured = cap != hipStreamCaptureStatusNone, wrap = !captured && lat->epoch + 2 * n + 3 >= (1ull << 31);
+        captured = cap != hipStreamCaptureStatusNone;
+        const bool wrap = !captured && lat->epoch + 2 * n + 3 >= (1ull << 31);
         if (captured || wrap) {
             const uint64_t words = halo_bytes(pl.nwg, lat->L) / 4;
             hipLaunchKernelGGL(k_zero_u32, dim3(static_cast<unsigned>((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
@@ -1093,8 +1098,9 @@ hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
         }
         if (wrap) lat->epoch = 0;
     }
+    const uint32_t epoch0 = captured ? 1u << 31 : static_cast<uint32_t>(lat->epoch);
     StripArgs a{lat->d_spins, lat->gen->d_state, lat->gen->S, lat->L, pl.R, pl.nwg, pl.units, T4, T8, n,
-                tr, lat->d_halo, static_cast<uint32_t>(lat->epoch), lat->d_err, hits, pl.R, 0, 0, bs.VB};
+                tr, lat->d_halo, epoch0, lat->d_err, hits, pl.R, 0, 0, bs.VB};
     void *args[] = {&a};
     hipError_t e;
     if (pl.nwg == 1)
@@ -1102,7 +1108,7 @@ hipError_t run_strips(Ising *lat, uint64_t T4, uint64_t T8, uint64_t n, int32_t 
     else
         e = hipLaunchCooperativeKernel(fn, dim3(pl.nwg), block, args, lds, st);
     if (e != hipSuccess) return e;
-    lat->epoch += 2 * n + 1;  // one tag per pass, one for the state before
+    if (!captured) lat->epoch += 2 * n + 1;  // one tag per pass, one for the state before
     return hipGetLastError();
 }
 

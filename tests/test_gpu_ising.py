@@ -648,3 +648,46 @@ def test_strips_in_a_graph(rngx, orc, kind, n, hits):
         if replay == 1:
             rngx.ising_sweep(lat, 0.42, 2, te)
             check(2, 1, te)
+
+
+@pytest.mark.parametrize("kind", ["mwc", "xs1024w"])
+@pytest.mark.parametrize("n", [1, 3])
+@pytest.mark.parametrize("first", [0])
+def test_graph_of_strips_outlives_its_plan(rngx, orc, kind, n, first):
+    """A graph captured under one plan goes on giving the oracle's lattice,
+    between eager calls, after plans of other strips, of none and a tuned one,
+    and writes to nothing but the lattice's own memory."""
+    L = 512
+    lat = rngx.ising_create(L, kind, 6)
+    plans = [p for p in rngx.ising_plans(lat) if p > 1]
+    rngx.ising_set_plan(lat, plans[first])
+    sp, st = orc.ising_create(L, kind, 6)
+    tr = torch.zeros(n, dtype=torch.int32, device="cuda")
+    te = torch.zeros(2, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        rngx.ising_sweep(lat, 0.42, n, tr)
+
+    def check(sweeps, got):
+        want = orc.ising_sweeps(L, kind, 0.42, st, sp, sweeps)
+        assert rngx.ising_status(lat) == 0
+        assert np.array_equal(got.cpu().numpy(), want)
+        assert np.array_equal(rngx.ising_get_spins(lat).ravel(), sp)
+        assert np.array_equal(rngx.rng_get_state(rngx.ising_rng(lat)), st)
+
+    for plan in (plans[-1], plans[0], 0, None, plans[-1]):
+        print(f"case strips graph under plan {plan} {kind} n={n}", flush=True)
+        if plan is None:
+            rngx.ising_autotune(lat, 0.42, 2, reps=1)
+        else:
+            rngx.ising_set_plan(lat, plan)
+        torch.cuda.empty_cache()
+        other = [torch.full((2 * strips * L,), 7, dtype=torch.int32, device="cuda") for strips in plans]
+        for _ in range(2):
+            g.replay()
+            torch.cuda.synchronize()
+            check(n, tr)
+            rngx.ising_sweep(lat, 0.42, 2, te)
+            check(2, te)
+        assert all(bool((t == 7).all()) for t in other)
