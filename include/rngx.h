@@ -245,8 +245,9 @@ rngx_status rng_autotune_fill(rngx_gen g, uint32_t *d_out, uint64_t count_per_st
  * ising_plans: the strip counts that fit this lattice, most strips first,
  * then 0 (from memory); strips_out (n entries) may be NULL to ask for
  * *n only.  ising_set_plan: use `strips` strips (0: from memory); synchronizes
- * the device.  The second image stays until ising_destroy, so that a graph
- * captured from sweeps in memory may be replayed under any later plan.
+ * the device.  What sweeps use beside the lattice (the second image, the
+ * strips' exchange buffers) stays until ising_destroy, so that a graph captured
+ * from sweeps may be replayed under any later plan.
  * ising_autotune: times every plan on `reps` (>= 1) calls of
  * n_sweeps sweeps at beta after one warm-up call, keeps the fastest and
  * restores the spins and stream states it started from (saved to device

@@ -685,6 +685,7 @@ static void free_tiles(Ising *lat) {
 static void free_ising(Ising *lat) {
     (void)hipFree(lat->d_spins);
     (void)hipFree(lat->d_halo);
+    for (uint64_t *h : lat->old_halos) (void)hipFree(h);
     (void)hipFree(lat->d_err);
     (void)hipFree(lat->d_partial);
     free_tiles(lat);
@@ -797,11 +798,14 @@ hipError_t apply_plan(Ising *lat, const IsingPlan &p) {
     hipError_t e = hipDeviceSynchronize();
     const uint64_t L = lat->L;
     if (e == hipSuccess && p.strips && p.nwg > 1 && p.nwg > lat->halo_nwg) {
-        (void)hipFree(lat->d_halo);
-        lat->d_halo = nullptr;
-        lat->halo_nwg = 0;
-        e = hipMalloc(&lat->d_halo, halo_bytes(p.nwg, L));
-        if (e == hipSuccess) lat->halo_nwg = p.nwg;
+        // the smaller one lives on: a graph captured under an earlier plan may hold it, as it may the second image
+        uint64_t *halo = nullptr;
+        e = hipMalloc(&halo, halo_bytes(p.nwg, L));
+        if (e == hipSuccess) {
+            if (lat->d_halo) lat->old_halos.push_back(lat->d_halo);
+            lat->d_halo = halo;
+            lat->halo_nwg = p.nwg;
+        }
     }
     if (e == hipSuccess && needs_partials(lat, p) && !lat->d_partial)
         e = hipMalloc(&lat->d_partial, 4 * ising_partials(lat->L));

@@ -100,6 +100,7 @@ struct Ising {
     IsingPlan plan;
     uint64_t *d_halo;    // strips: halo_bytes of tagged words (spins | pass tag << 32)
     uint32_t halo_nwg;   // strips the halo allocation is sized for
+    std::vector<uint64_t *> old_halos;  // smaller ones that captured graphs may hold
     uint32_t *d_err;     // strips: set if a neighbour wait gave up
     int32_t *d_partial;  // per-pass path: per-block energy partials (null where no sweep takes it)
     int8_t *alt_spins;   // tiled sweeps: the images every second block writes (null where sweeps run per pass)

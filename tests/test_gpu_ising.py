@@ -652,7 +652,7 @@ def test_strips_in_a_graph(rngx, orc, kind, n, hits):
 
 @pytest.mark.parametrize("kind", ["mwc", "xs1024w"])
 @pytest.mark.parametrize("n", [1, 3])
-@pytest.mark.parametrize("first", [0])
+@pytest.mark.parametrize("first", [0, -1])
 def test_graph_of_strips_outlives_its_plan(rngx, orc, kind, n, first):
     """A graph captured under one plan goes on giving the oracle's lattice,
     between eager calls, after plans of other strips, of none and a tuned one,
